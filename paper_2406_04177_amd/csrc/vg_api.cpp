@@ -92,18 +92,17 @@ size_t layout(vg_sim *h, char *base) {
         h->cg_y = (double *)take(nd);
         h->cg_r = (double *)take(nd);
         h->cg_z = (double *)take(nd);
-        h->cg_q = (double *)take(nd);
         h->cg_m = (double *)take(nd);
         h->cg_p[0] = (double *)take(nd);
         h->cg_p[1] = (double *)take(nd);
         h->cg_part = (double *)take(sizeof(double) * 4 * (size_t)h->cg_blocks);
-        h->cg_scal = (double *)take(sizeof(double) * 8);
+        h->cg_scal = (double *)take(sizeof(double) * 16);
     }
     if (h->features & VG_FEAT_MG) {
         // the hierarchy at the capacities mg_plan reserved (set-up scratch:
         // the occupancy bytes of the largest coarse grid)
-        h->mg[0].parent = (int32_t *)take(sizeof(int32_t) * (size_t)h->n);
-        h->mg[0].e = (double *)take(sizeof(double) * (size_t)h->n);   // fine residual / prolongated iterate
+        h->mg[0].parent = (uint32_t *)take(sizeof(uint32_t) * (size_t)h->n);
+        h->mg[0].e = (double *)take(sizeof(double) * (size_t)h->n);   // fine residual
         size_t mask = 1;
         for (int l = 1; l < h->mg_plan_levels; l++) {
             vg_sim::MgLevel &L = h->mg[l];
@@ -116,7 +115,7 @@ size_t layout(vg_sim *h, char *base) {
             L.r = (double *)take(sizeof(double) * cap);
             L.x = (double *)take(sizeof(double) * cap);
             L.e = (double *)take(sizeof(double) * cap);
-            L.parent = (int32_t *)take(sizeof(int32_t) * cap);
+            L.parent = (uint32_t *)take(sizeof(uint32_t) * cap);
             size_t rb = 0;
             vg_rank_bytes(L.nx, L.ny, L.nz, 0, &rb);
             L.rank = (RankWord *)take(rb);

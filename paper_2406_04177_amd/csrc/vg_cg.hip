@@ -5,20 +5,28 @@
 // neighbour source: table or packed).  Vectors,
 // dot products and scalars are FP64 whatever the field type.
 //
-// Per iteration two streaming kernels, each followed by a one-block kernel
-// that reduces the per-block partials in a fixed order and updates the
-// scalars on the device:
-//  - SpMV: the new direction p = z + beta p_old, q = B p and p.q partials;
-//    also x += alpha p_old, the previous iteration's x update, done here
-//    where p_old is read anyway (the last one is added on write-back);
-//  - update: r -= alpha q, z = M^-1 r, r.z and r.r partials (without region
-//    weights M^-1 comes from a table indexed by the voxel's neighbour count,
-//    1 byte per voxel instead of an FP64 vector).
-// q = B p is formed as B z + beta q_old (linearity), so the SpMV gathers one
-// vector instead of two; this adds rounding to the gap between the recursive
-// and the true residual, orders of magnitude below the tolerances in use.
-// The host reads the scalars only every few iterations; kernels launched
-// after convergence return at once.
+// Both kernels of an iteration are bound by memory, so the iteration is cut
+// to move as few bytes as it can:
+//  - k_cg_dot: the partials of (z, B z), a gather of z and the neighbour
+//    words and nothing else (12.5 B per voxel).  (p, B p) follows from it:
+//    with p = z + beta p_old, z.r_old = 0 and p.B p_old = 0,
+//    (p, B p) = (z, B z) - beta (r.z) / alpha_old
+//    (Chronopoulos and Gear, J. Comput. Appl. Math. 25, 1989);
+//  - k_cg_step: p = z + beta p_old for the voxel and its neighbours, so that
+//    q = B p is formed in registers and never stored; z <- z - alpha M^-1 q
+//    into the other z buffer (r = M z is not stored: r_i is z_i times the
+//    diagonal), p into the other p buffer, and every second iteration
+//    x += alpha_old p_old + alpha p (a last odd direction is added on
+//    write-back); the partials of r.z and r.r.  28.5 B read, 16 B written per
+//    voxel and 16 B for x every second iteration.
+// 57 B per voxel and iteration on average.  (The form before it stored q, r
+// and updated x each time: 93.5 B; 512^3, 22.8 M voxels: see k_cg_step.)
+// There is no kernel for the scalars: each block of the kernel that needs
+// them adds up the partials of the kernel before it, in a fixed order, and
+// block 0 keeps the results for later kernels in slots no block of the same
+// kernel reads.  The host reads the scalars only every few iterations (the
+// number follows the convergence seen so far); kernels launched after
+// convergence return at once.
 //
 // Multigrid option (not in the paper, whose preconditioner is the diagonal):
 // M^-1 is one V-cycle over a hierarchy of aggregates.  Level l+1 has one cell
@@ -37,16 +45,43 @@
 // children (found with the level's rank index in a fixed order) and the
 // prolongation per fine cell from its parent, so no sum depends on
 // scheduling.  Every level's kernels are one thread per cell: residual,
-// restriction (sum over the children), prolongation (add the parent's
-// value), post-smoothing.  In MG mode the update kernel also forms the
-// pre-smoothed iterate w D^-1 r (in z); the V-cycle's last kernel writes z
-// and the r.z partials.
+// restriction (sum over the children), then prolongation and post-smoothing
+// in one.  With t = r - B x the residual of the pre-smoothed x, and P e the
+// prolongated coarse solution, the post-smoothed result is
+//   y + w D^-1 (r - B y) = x + P e + w D^-1 (t - B P e),  y = x + P e,
+// and P e is constant on every 2x2x2 block: of a cell's six neighbours three
+// lie in its own block (their terms vanish) and the others in the three
+// coarse neighbours on its side, so this kernel gathers only from the four
+// times smaller coarse solution.  With the multigrid r is kept (in place of
+// the z update) and the V-cycle writes z and the r.z partials.
+#include <type_traits>
+
 #include "vg_internal.h"
 
 namespace vg {
 namespace {
 
-enum { S_RZ = 0, S_RR, S_BB, S_ALPHA, S_BETA, S_DONE, S_ITER, S_RTOL2, S_NSCAL = 8 };
+// Scalars on the device: r.z and alpha of the current and the previous
+// iteration (slot = iteration & 1), r.r, b.b, the convergence flag, the
+// iterations done and the squared tolerance.
+enum { S_RZ = 0, S_ALPHA = 2, S_RR = 4, S_BB, S_DONE, S_ITER, S_RTOL2, S_NSCAL = 9 };
+// Partials per block, one array of CgArgs::ldp each: r.z, r.r, b.b, z.Bz.
+enum { P_RZ = 0, P_RR, P_BB, P_ZBZ };
+
+// The gathering kernels come in two forms.  A 64-lane load of doubles takes
+// the vector cache 16 cycles whatever its addresses (measured: 17.8 accesses
+// per load), so a voxel's seven values of one vector cost more than their
+// memory traffic.  The staged form puts a block's tile of kCgTileV * kBlock
+// consecutive voxels and a halo of kCgHalo voxels on each side into LDS by
+// contiguous loads, reads the x and y neighbours there (4 cycles per wave)
+// and gathers only the z neighbours; it needs the x and y distances to fit
+// the halo, and enough voxels that every CU has tiles (kCgStagedMin).  The
+// direct form, one voxel per thread, serves the rest.
+constexpr int kCgTileV = 4;
+constexpr int kMgPostV = 2;      // voxels per thread of the V-cycle's last kernel
+constexpr int kCgHalo = 256;
+constexpr int64_t kCgStagedMin = (int64_t)1 << 20;
+constexpr int kCgMaxBlocks = 2048;      // partials per slot at most (vg_sim::cg_blocks)
 
 // multigrid V-cycle
 constexpr double kMgOmega = 0.8;        // damping of the Jacobi smoother
@@ -72,6 +107,8 @@ struct CgArgs {
     int64_t ntiles = 0;
     double a = 0;
     double c[VG_NREG] = {};
+    int ldp = 0;                 // partials per slot
+    uint32_t run = kXcdRun;      // block tiles per XCD run (xcd_run)
 };
 
 // Neighbour sources of the CG kernels (the explicit step's): the table, or
@@ -99,22 +136,159 @@ __device__ __forceinline__ void cg_neighbours(const CgArgs &A, int64_t i, int64_
     }
 }
 
+// Index type: 32 bits with a packed source (one address register per lane
+// beside the array's base; the host takes the table where n doubles do not
+// fit 2^32 bytes), 64 with the table.
+template <int NS>
+using CgIdx = std::conditional_t<NS == NS_TABLE, int64_t, uint32_t>;
+template <typename T>
+__device__ __forceinline__ T &el(T *b, uint32_t i) {
+    return at(b, i);
+}
+template <typename T>
+__device__ __forceinline__ T &el(T *b, int64_t i) {
+    return b[i];
+}
+
+// What the kernels load ahead of a voxel's gathers: its neighbour words (the
+// table's six indices, or the packed words and, for relative codes, the six
+// base distances of its group of 64: the same for the wave's lanes).
+template <int NS>
+struct CgWords {
+    int32_t jt[NS == NS_TABLE ? 6 : 1];
+    PackedWords W;
+    uint32_t base[NS == NS_REL ? 6 : 1];
+};
+
+template <int NS>
+__device__ __forceinline__ void cg_words(const CgArgs &A, CgIdx<NS> i, CgWords<NS> &w) {
+    w.W = PackedWords{0, 0};
+    if constexpr (NS == NS_TABLE) {
+#pragma unroll
+        for (int k = 0; k < 6; k++) w.jt[k] = A.nbr[(int64_t)k * A.n + i];
+    } else {
+        w.W = packed_words<NS == NS_REL>(A.pk, (uint32_t)i);
+        if constexpr (NS == NS_REL) {
+            const uint32_t grp = __builtin_amdgcn_readfirstlane((uint32_t)i / (uint32_t)kGroup);
+            const uint32_t *bp = A.pk.rel_base + (size_t)grp * 8;
+#pragma unroll
+            for (int k = 0; k < 6; k++) w.base[k] = *(const __attribute__((address_space(4))) uint32_t *)(bp + k);
+        }
+    }
+}
+
+// The neighbours (an absent one is the voxel itself).
+template <int NS>
+__device__ __forceinline__ void cg_decode(const CgArgs &A, CgIdx<NS> i, const CgWords<NS> &w, CgIdx<NS> (&j)[6],
+                                          bool (&pres)[6]) {
+    if constexpr (NS == NS_TABLE) {
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            pres[k] = w.jt[k] >= 0;
+            j[k] = pres[k] ? (int64_t)w.jt[k] : i;
+        }
+    } else if constexpr (NS == NS_REL) {
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            const uint32_t c = (w.W.a >> A.pk.rl.sh[k]) & A.pk.rl.mk[k];
+            const uint32_t d = w.base[k] + (c ? c - 1u : 0u), last = (uint32_t)A.n - 1u;
+            j[k] = (k & 1) ? min(i + d, last) : i - min(d, i);
+            pres[k] = c != 0;
+        }
+    } else {
+        uint32_t jp[6];
+        packed_decode<false>(A.pk, (uint32_t)i, w.W, jp);
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            j[k] = jp[k];
+            pres[k] = j[k] != i;
+        }
+    }
+}
+
+// The voxels of a thread in block tile t (clamped to the last voxel).
+template <int V, typename I>
+__device__ __forceinline__ void cg_own(const CgArgs &A, int64_t t, I (&i)[V], bool (&act)[V]) {
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+        const int64_t x = (t * V + v) * kBlock + threadIdx.x;
+        act[v] = x < A.n;
+        i[v] = (I)(act[v] ? x : A.n - 1);
+    }
+}
+
+// Staged form: the window of a tile in LDS, win[q] = voxel t0 - kCgHalo + q;
+// a thread's halo voxels (clamped into the volume: a clamped one is nobody's
+// neighbour).
+constexpr int kCgWin = kCgTileV * kBlock + 2 * kCgHalo;
+static_assert(kCgHalo == kBlock, "one halo voxel per thread and side");
+__device__ __forceinline__ void cg_halo(const CgArgs &A, int64_t t, uint32_t (&hi)[2]) {
+    const int64_t t0 = t * kCgTileV * kBlock, lo = t0 - kCgHalo + threadIdx.x,
+                  up = t0 + kCgTileV * kBlock + threadIdx.x;
+    hi[0] = (uint32_t)(lo > 0 ? lo : 0);
+    hi[1] = (uint32_t)(up < A.n ? up : A.n - 1);
+}
+__device__ __forceinline__ void cg_stage(double *win, const double (&own)[kCgTileV], const double (&halo)[2]) {
+    win[threadIdx.x] = halo[0];
+#pragma unroll
+    for (int v = 0; v < kCgTileV; v++) win[kCgHalo + v * kBlock + threadIdx.x] = own[v];
+    win[kCgHalo + kCgTileV * kBlock + threadIdx.x] = halo[1];
+    lds_barrier();
+}
+
+// Sum of the G per-block partials of a slot, the same in every thread of the
+// block, in a fixed order.  lds: kWaves doubles.
+__device__ __forceinline__ double reduce_parts(const double *__restrict__ part, int G,
+                                               double *lds) {
+    // all loads in flight at once (one after the other they cost the start of
+    // the kernel a memory latency each)
+    constexpr int U = kCgMaxBlocks / kBlock;
+    double x[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int b = u * kBlock + (int)threadIdx.x;
+        x[u] = b < G ? part[b] : 0.0;
+    }
+    double v = x[0];
+#pragma unroll
+    for (int u = 1; u < U; u++) v += x[u];
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = lds[0];
+    for (int w = 1; w < kWaves; w++) v += lds[w];
+    __syncthreads();
+    return v;
+}
+
+// Convergence of iterate k (k iterations done) from the G partials of r.r;
+// block 0 keeps the scalars.  True in every thread once converged.
+__device__ __forceinline__ bool cg_check(const double *__restrict__ rr_part, int G, int k, double bb,
+                                         double *__restrict__ scal, double *lds) {
+    const double rr = reduce_parts(rr_part, G, lds);
+    const bool done = rr <= scal[S_RTOL2] * bb;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        scal[S_RR] = rr;
+        scal[S_ITER] = (double)k;
+        if (done) scal[S_DONE] = 1.0;
+    }
+    return done;
+}
+
+// Start: y = b, r = b - B b; z = M^-1 r (Jacobi), or r for the V-cycle.
 template <typename F, bool REG, int NS, bool MG>
-__global__ __launch_bounds__(kBlock) void k_cg_init(CgArgs A, F field,
-                                                    double *__restrict__ y, double *__restrict__ r,
-                                                    double *__restrict__ z, double *__restrict__ p,
-                                                    double *__restrict__ m, double *__restrict__ part,
-                                                    double *__restrict__ q) {
+__global__ __launch_bounds__(kBlock) void k_cg_init(CgArgs A, F field, double *__restrict__ y,
+                                                    double *__restrict__ rz, double *__restrict__ m,
+                                                    double *__restrict__ part) {
     __shared__ double lds[kWaves * 3];
     __shared__ double cl[VG_NREG];
     if (threadIdx.x < VG_NREG) cl[threadIdx.x] = A.c[threadIdx.x];
     __syncthreads();
     double acc[3] = {0.0, 0.0, 0.0};   // r.z, r.r, b.b
     for (int64_t it = 0;; it++) {
-    const int64_t t = xcd_stride_tile(blockIdx.x, gridDim.x, it, A.ntiles);
-    if (t >= A.ntiles) break;
-    for (int v = 0; v < kVPT; v++) {
-        const int64_t i = t * kTile + v * kBlock + threadIdx.x;
+        const int64_t t = xcd_stride_tile(blockIdx.x, gridDim.x, it, A.ntiles);
+        if (t >= A.ntiles) break;
+        const int64_t i = t * kTile + threadIdx.x;
         if (i >= A.n) continue;
         const double b = field.get(i);
         int64_t j[6];
@@ -133,157 +307,253 @@ __global__ __launch_bounds__(kBlock) void k_cg_init(CgArgs A, F field,
         }
         const double mi = 1.0 / (1.0 + A.a * deg);
         const double ri = b - (b + A.a * s);
-        const double zi = mi * ri;
         y[i] = b;
-        r[i] = ri;
-        // MG: z holds the V-cycle's pre-smoothed iterate w D^-1 r until the
-        // cycle overwrites it; the first direction is then z + 0 * p
-        z[i] = MG ? kMgOmega * ri * mi : zi;
-        p[i] = MG ? 0.0 : zi;
+        rz[i] = MG ? ri : mi * ri;
         if (REG) m[i] = mi;
         else ((uint8_t *)m)[i] = (uint8_t)deg;   // 1/diag is then one of 7 values
-        q[i] = 0.0;    // B p of no direction: the first q is B z alone (beta = 0)
-        acc[0] += ri * zi;
+        acc[0] += ri * (mi * ri);
         acc[1] += ri * ri;
         acc[2] += b * b;
     }
-    }
     block_sum<3>(acc, lds);
     if (threadIdx.x == 0) {
-        for (int u = MG ? 1 : 0; u < 3; u++) part[(int64_t)blockIdx.x * 4 + u] = acc[u];
+        for (int u = MG ? 1 : 0; u < 3; u++) part[u * A.ldp + (int)blockIdx.x] = acc[u];
     }
 }
 
-// p' = z + beta p (the new search direction, written out) and q' = B p',
-// formed as B z + beta q by linearity so that only z is gathered (q holds
-// B p from the previous iteration and 0 before the first, where beta = 0)
-template <bool REG, int NS>
-__global__ __launch_bounds__(kBlock) void k_cg_spmv(CgArgs A, const double *__restrict__ z,
-                                                    const double *__restrict__ pold, double *__restrict__ pnew,
-                                                    double *__restrict__ y,
-                                                    double *__restrict__ q, const double *__restrict__ scal,
-                                                    double *__restrict__ part) {
+// Partials of (z, B z) of iteration k; before that r.z of iterate k from its
+// Gp partials, and for Jacobi the convergence check (the V-cycle has done it).
+// In every gathering kernel a tile's neighbour words are loaded one tile
+// ahead, so that its gathers wait for nothing; the staged window is double
+// buffered (one barrier per tile).
+// 512^3 (22.8 M voxels): 125 us direct, 92 us staged (12.5 B per voxel).
+template <bool REG, int NS, bool MG, int V>
+__global__ __launch_bounds__(kBlock) void k_cg_dot(CgArgs A, int k, int Gp, const double *__restrict__ z,
+                                                   double *__restrict__ scal, double *__restrict__ part) {
     if (scal[S_DONE] != 0.0) return;
-    __shared__ double lds[kWaves];
+    constexpr bool ST = V > 1;
+    __shared__ double win[ST ? 2 : 1][ST ? kCgWin : 1];
+    __shared__ double lds[kWaves * 2];
     __shared__ double cl[VG_NREG];
     if (threadIdx.x < VG_NREG) cl[threadIdx.x] = A.c[threadIdx.x];
     __syncthreads();
-    const double beta = scal[S_BETA], alpha = scal[S_ALPHA];
-    double acc[1] = {0.0};
-    for (int64_t it = 0;; it++) {
-    const int64_t t = xcd_stride_tile(blockIdx.x, gridDim.x, it, A.ntiles);
-    if (t >= A.ntiles) break;
-    for (int v = 0; v < kVPT; v++) {
-        const int64_t i = t * kTile + v * kBlock + threadIdx.x;
-        if (i >= A.n) continue;
-        const double zi = z[i], po = pold[i];
-        y[i] += alpha * po;   // the previous iteration's x update (alpha = 0 before the first)
-        const double pi = zi + beta * po;
-        int64_t j[6];
-        bool pres[6];
-        cg_neighbours<NS>(A, i, j, pres);
-        double zj[6];
-#pragma unroll
-        for (int k = 0; k < 6; k++) zj[k] = z[j[k]];
-        double s = 0.0;
-#pragma unroll
-        for (int k = 0; k < 6; k++) {
-            if (!pres[k]) continue;
-            s += weight(A.rcode, cl, i, k, REG) * (zi - zj[k]);
-        }
-        const double qi = (zi + A.a * s) + beta * q[i];
-        pnew[i] = pi;
-        q[i] = qi;
-        acc[0] += pi * qi;
+    if (!MG && cg_check(part + P_RR * A.ldp, Gp, k, scal[S_BB], scal, lds)) return;
+    if (blockIdx.x == 0) {
+        const double rz = reduce_parts(part + P_RZ * A.ldp, Gp, lds);
+        if (threadIdx.x == 0) scal[S_RZ + (k & 1)] = rz;
     }
+    const int64_t nt = (A.n + kBlock * V - 1) / (kBlock * V);
+    double acc[1] = {0.0};
+    int64_t t = xcd_stride_tile(blockIdx.x, gridDim.x, 0, nt, A.run);
+    CgIdx<NS> i[V];
+    bool act[V];
+    CgWords<NS> w[V];
+    cg_own(A, t, i, act);
+#pragma unroll
+    for (int v = 0; v < V; v++) cg_words<NS>(A, i[v], w[v]);
+    for (int64_t it = 1; t < nt; it++) {
+        bool pres[V][6];
+        double zi[V], zj[V][6];
+        [[maybe_unused]] uint32_t q[V][4];
+        [[maybe_unused]] double hz[2];
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            CgIdx<NS> j[6];
+            cg_decode<NS>(A, i[v], w[v], j, pres[v]);
+            zi[v] = el(z, i[v]);
+#pragma unroll
+            for (int k6 = ST ? 4 : 0; k6 < 6; k6++) zj[v][k6] = el(z, j[k6]);
+            if constexpr (ST) {
+#pragma unroll
+                for (int k4 = 0; k4 < 4; k4++) q[v][k4] = (uint32_t)(j[k4] - (uint32_t)(t * V * kBlock)) + kCgHalo;
+            }
+        }
+        if constexpr (ST) {
+            uint32_t hi[2];
+            cg_halo(A, t, hi);
+            hz[0] = el(z, hi[0]);
+            hz[1] = el(z, hi[1]);
+        }
+        t = xcd_stride_tile(blockIdx.x, gridDim.x, it, nt, A.run);
+        CgIdx<NS> in[V];
+        bool an[V];
+        cg_own(A, t, in, an);
+#pragma unroll
+        for (int v = 0; v < V; v++) cg_words<NS>(A, in[v], w[v]);
+        if constexpr (ST) {
+            double *wb = win[it & 1];
+            cg_stage(wb, zi, hz);
+#pragma unroll
+            for (int v = 0; v < V; v++)
+#pragma unroll
+                for (int k4 = 0; k4 < 4; k4++) zj[v][k4] = wb[q[v][k4]];
+        }
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            double s = 0.0;
+#pragma unroll
+            for (int k6 = 0; k6 < 6; k6++) {
+                const double wt = weight(A.rcode, cl, i[v], k6, REG);
+                s += pres[v][k6] ? wt * (zi[v] - zj[v][k6]) : 0.0;
+            }
+            acc[0] += act[v] ? zi[v] * (zi[v] + A.a * s) : 0.0;
+            i[v] = in[v];
+            act[v] = an[v];
+        }
     }
     block_sum<1>(acc, lds);
-    if (threadIdx.x == 0) part[(int64_t)blockIdx.x * 4] = acc[0];
+    if (threadIdx.x == 0) part[P_ZBZ * A.ldp + (int)blockIdx.x] = acc[0];
 }
 
-// m: 1/diag per voxel with region weights; without them the number of
-// neighbours per voxel (uint8), and 1/diag = 1 / (1 + a deg) from a table
-// (the same division as in the init kernel, so the same values)
-template <bool REG, bool MG>
-__global__ __launch_bounds__(kBlock) void k_cg_update(int64_t n, int64_t ntiles, double a,
-                                                      const double *__restrict__ q, const double *__restrict__ m,
-                                                      double *__restrict__ r,
-                                                      double *__restrict__ z, const double *__restrict__ scal,
-                                                      double *__restrict__ part) {
+// Iteration k's update: alpha and beta from the Gp partials of (z, B z), p = z + beta p_old
+// (for the neighbours too), q = B p, then z' = z - alpha M^-1 q (Jacobi, into
+// zr) or r -= alpha q (MG, zr in place).  Odd k also add the last two
+// directions to y.  512^3: 325 us direct, 255 us staged (52.5 B per voxel on
+// average); the two kernels that stored q and r took 343 and 151 us.
+template <bool REG, int NS, bool MG, int V>
+__global__ __launch_bounds__(kBlock) void k_cg_step(CgArgs A, int k, int Gp, const double *__restrict__ z,
+                                                    const double *__restrict__ pold, double *__restrict__ pnew,
+                                                    double *__restrict__ y, double *__restrict__ zr,
+                                                    double *__restrict__ scal, double *__restrict__ part) {
     if (scal[S_DONE] != 0.0) return;
+    constexpr bool ST = V > 1;
+    __shared__ double win[ST ? 2 : 1][ST ? kCgWin : 1];
     __shared__ double lds[kWaves * 2];
+    __shared__ double cl[VG_NREG];
     __shared__ double mtab[8];
-    if (!REG) {
-        if (threadIdx.x < 7) mtab[threadIdx.x] = 1.0 / (1.0 + a * (double)threadIdx.x);
-        __syncthreads();
-    }
-    const double alpha = scal[S_ALPHA];
+    if (threadIdx.x < VG_NREG) cl[threadIdx.x] = A.c[threadIdx.x];
+    if (!MG && !REG && threadIdx.x < 7) mtab[threadIdx.x] = 1.0 / (1.0 + A.a * (double)threadIdx.x);
+    __syncthreads();
+    const double zbz = reduce_parts(part + P_ZBZ * A.ldp, Gp, lds);
+    const double rz = scal[S_RZ + (k & 1)];
+    const double aold = k > 0 ? scal[S_ALPHA + ((k & 1) ^ 1)] : 0.0;
+    const double beta = k > 0 ? rz / scal[S_RZ + ((k & 1) ^ 1)] : 0.0;
+    const double alpha = k > 0 ? rz / (zbz - beta * rz / aold) : rz / zbz;
+    if (blockIdx.x == 0 && threadIdx.x == 0) scal[S_ALPHA + (k & 1)] = alpha;
+    const bool add = (k & 1) != 0, first = k == 0;   // p_old holds nothing before the first direction
+    const int64_t nt = (A.n + kBlock * V - 1) / (kBlock * V);
     double acc[2] = {0.0, 0.0};
-    for (int64_t it = 0;; it++) {
-    const int64_t t = xcd_stride_tile(blockIdx.x, gridDim.x, it, ntiles);
-    if (t >= ntiles) break;
-    for (int v = 0; v < kVPT; v++) {
-        const int64_t i = t * kTile + v * kBlock + threadIdx.x;
-        if (i >= n) continue;
-        const double ri = r[i] - alpha * q[i];
-        const double mi = REG ? m[i] : mtab[((const uint8_t *)m)[i]];
-        r[i] = ri;
-        if (MG) {
-            z[i] = kMgOmega * ri * mi;   // the V-cycle's pre-smoothed iterate
-        } else {
-            const double zi = mi * ri;
-            z[i] = zi;
-            acc[0] += ri * zi;
+    int64_t t = xcd_stride_tile(blockIdx.x, gridDim.x, 0, nt, A.run);
+    CgIdx<NS> i[V];
+    bool act[V];
+    CgWords<NS> w[V];
+    cg_own(A, t, i, act);
+#pragma unroll
+    for (int v = 0; v < V; v++) cg_words<NS>(A, i[v], w[v]);
+    for (int64_t it = 1; t < nt; it++) {
+        constexpr int K0 = ST ? 4 : 0;   // the slots gathered from memory
+        bool pres[V][6];
+        double zi[V], po[V], zj[V][6], oj[V][6], yi[V], ri[V];
+        [[maybe_unused]] uint32_t q[V][4];
+        [[maybe_unused]] double hz[2], ho[2];
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            CgIdx<NS> j[6];
+            cg_decode<NS>(A, i[v], w[v], j, pres[v]);
+            zi[v] = el(z, i[v]);
+            po[v] = first ? 0.0 : el(pold, i[v]);
+#pragma unroll
+            for (int k6 = K0; k6 < 6; k6++) zj[v][k6] = el(z, j[k6]);
+#pragma unroll
+            for (int k6 = K0; k6 < 6; k6++) oj[v][k6] = first ? 0.0 : el(pold, j[k6]);
+            yi[v] = add ? el(y, i[v]) : 0.0;
+            ri[v] = MG ? el(zr, i[v]) : 0.0;
+            if constexpr (ST) {
+#pragma unroll
+                for (int k4 = 0; k4 < 4; k4++) q[v][k4] = (uint32_t)(j[k4] - (uint32_t)(t * V * kBlock)) + kCgHalo;
+            }
         }
-        acc[1] += ri * ri;
-    }
+        if constexpr (ST) {
+            uint32_t hi[2];
+            cg_halo(A, t, hi);
+#pragma unroll
+            for (int u = 0; u < 2; u++) {
+                hz[u] = el(z, hi[u]);
+                ho[u] = first ? 0.0 : el(pold, hi[u]);
+            }
+        }
+        t = xcd_stride_tile(blockIdx.x, gridDim.x, it, nt, A.run);
+        CgIdx<NS> in[V];
+        bool an[V];
+        cg_own(A, t, in, an);
+#pragma unroll
+        for (int v = 0; v < V; v++) cg_words<NS>(A, in[v], w[v]);
+        // p = z + beta p_old of the voxel (po becomes it below) and its neighbours
+        double pi[V];
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            pi[v] = zi[v] + beta * po[v];
+#pragma unroll
+            for (int k6 = K0; k6 < 6; k6++) zj[v][k6] += beta * oj[v][k6];
+        }
+        if constexpr (ST) {
+#pragma unroll
+            for (int u = 0; u < 2; u++) hz[u] += beta * ho[u];
+            double *wb = win[it & 1];
+            cg_stage(wb, pi, hz);
+#pragma unroll
+            for (int v = 0; v < V; v++)
+#pragma unroll
+                for (int k4 = 0; k4 < 4; k4++) zj[v][k4] = wb[q[v][k4]];
+        }
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            double s = 0.0, deg = 0.0;
+#pragma unroll
+            for (int k6 = 0; k6 < 6; k6++) {
+                const double wt = weight(A.rcode, cl, i[v], k6, REG);
+                deg += pres[v][k6] ? wt : 0.0;
+                s += pres[v][k6] ? wt * (pi[v] - zj[v][k6]) : 0.0;
+            }
+            const double qi = pi[v] + A.a * s;
+            double rn, zn = 0.0;
+            if (MG) {
+                rn = ri[v] - alpha * qi;
+            } else {
+                const double di = 1.0 + A.a * deg;
+                const double mi = REG ? 1.0 / di : mtab[(int)deg];
+                zn = zi[v] - alpha * (mi * qi);
+                rn = di * zn;
+            }
+            if (act[v]) {
+                el(pnew, i[v]) = pi[v];
+                if (add) el(y, i[v]) = yi[v] + (aold * po[v] + alpha * pi[v]);
+                el(zr, i[v]) = MG ? rn : zn;
+                acc[0] += rn * zn;
+                acc[1] += rn * rn;
+            }
+            i[v] = in[v];
+            act[v] = an[v];
+        }
     }
     block_sum<2>(acc, lds);
     if (threadIdx.x == 0) {
-        if (!MG) part[(int64_t)blockIdx.x * 4] = acc[0];   // MG: the V-cycle writes r.z
-        part[(int64_t)blockIdx.x * 4 + 1] = acc[1];
+        if (!MG) part[P_RZ * A.ldp + (int)blockIdx.x] = acc[0];   // MG: the V-cycle writes r.z
+        part[P_RR * A.ldp + (int)blockIdx.x] = acc[1];
     }
 }
 
-// stage 0: after init; 1: alpha after spmv; 2: beta/convergence after update
-__global__ __launch_bounds__(kBlock) void k_cg_scalars(const double *__restrict__ part, int nblocks, int stage,
-                                                       double *__restrict__ scal) {
-    if (stage != 0 && scal[S_DONE] != 0.0) return;
-    __shared__ double lds[kWaves * 3];
-    double v[3] = {0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < nblocks; b += kBlock) {
-        v[0] += part[(int64_t)b * 4];
-        v[1] += part[(int64_t)b * 4 + 1];
-        v[2] += part[(int64_t)b * 4 + 2];
+// The scalars of iterate k for the host (one block); k = 0: b.b too.
+__global__ __launch_bounds__(kBlock) void k_cg_status(int ldp, int Gp, int k, double *__restrict__ scal,
+                                                      const double *__restrict__ part) {
+    if (scal[S_DONE] != 0.0) return;
+    __shared__ double lds[kWaves];
+    double bb = scal[S_BB];
+    if (k == 0) {
+        bb = reduce_parts(part + P_BB * ldp, Gp, lds);
+        if (threadIdx.x == 0) scal[S_BB] = bb;
     }
-    block_sum<3>(v, lds);
-    if (threadIdx.x != 0) return;
-    if (stage == 0) {
-        scal[S_RZ] = v[0];
-        scal[S_RR] = v[1];
-        scal[S_BB] = v[2];
-        scal[S_BETA] = 0.0;
-        scal[S_ITER] = 0.0;
-        scal[S_DONE] = (v[1] <= scal[S_RTOL2] * v[2]) ? 1.0 : 0.0;
-    } else if (stage == 1) {
-        scal[S_ALPHA] = scal[S_RZ] / v[0];
-    } else {
-        scal[S_BETA] = v[0] / scal[S_RZ];
-        scal[S_RZ] = v[0];
-        scal[S_RR] = v[1];
-        scal[S_ITER] = scal[S_ITER] + 1.0;
-        if (v[1] <= scal[S_RTOL2] * scal[S_BB]) scal[S_DONE] = 1.0;
-    }
+    cg_check(part + P_RR * ldp, Gp, k, bb, scal, lds);
 }
 
-// the solution with the last direction's update still to add, rounded to the
-// field storage
+// The solution, rounded to the field storage; an odd number of iterations
+// leaves the last direction to add (p: the buffer that holds it).
 template <typename F>
 __global__ __launch_bounds__(kBlock) void k_cg_writeback(int64_t n, const double *__restrict__ y,
-                                                         const double *__restrict__ p,
+                                                         const double *__restrict__ p, int add,
                                                          const double *__restrict__ scal, F field) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) field.put(i, y[i] + scal[S_ALPHA] * p[i]);
+    if (i < n) field.put(i, add ? y[i] + scal[S_ALPHA] * p[i] : y[i]);
 }
 
 // ---------------------------------------------------------------- multigrid
@@ -294,7 +564,7 @@ struct MgView {
     const float *w, *mass;
     const double *invd;
     double *r, *x, *e;
-    const int32_t *parent;
+    const uint32_t *parent;
     const RankWord *rank;
     const int32_t *vox;
     int64_t n, ld;
@@ -303,9 +573,9 @@ struct MgView {
 
 // Diagonal inverse of the fine level, 1 / (1 + a sum_j w_ij): from the
 // vector the init kernel wrote (region weights) or from the neighbour count.
-template <bool REG>
-__device__ __forceinline__ double fine_minv(const double *m, const double *mtab, int64_t i) {
-    return REG ? m[i] : mtab[((const uint8_t *)m)[i]];
+template <bool REG, typename I>
+__device__ __forceinline__ double fine_minv(const double *m, const double *mtab, I i) {
+    return REG ? el(m, i) : mtab[el((const uint8_t *)m, i)];
 }
 
 // Calls f(i, d) for the cells i of level l inside cell (X, Y, Z) of level
@@ -347,16 +617,39 @@ __global__ __launch_bounds__(kBlock) void k_mg_mark(const int32_t *__restrict__ 
     mask[(x >> 1) + (int64_t)cnx * ((y >> 1) + (int64_t)cny * (z >> 1))] = 1;
 }
 
-// set-up: the cell of the next level that holds each cell
+// set-up: the cell of the next level that holds each cell, in the low 27
+// bits (the grids are at most 1024^3, so a coarse one has at most 2^27
+// cells), and above them the cell's outer neighbours (those outside its
+// 2x2x2 block, one per axis) as a base-3 number, x first: per axis 0 absent,
+// 1 on the minus side (even coordinate), 2 on the plus side.
+constexpr int kParentBits = 27;
 __global__ __launch_bounds__(kBlock) void k_mg_parent(const int32_t *__restrict__ vox, int64_t n, int nx, int ny,
                                                       const RankWord *__restrict__ crank, Geom cg,
-                                                      int32_t *__restrict__ parent) {
+                                                      const int32_t *__restrict__ nbr, int64_t ld,
+                                                      uint32_t *__restrict__ parent) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
     int x, y, z;
     mg_cell_xyz(vox, i, nx, ny, x, y, z);
     const int64_t p = geom_pos(cg, x >> 1, y >> 1, z >> 1);
-    parent[i] = rank_lookup(crank[p >> 5], (uint32_t)p);
+    const int odd[3] = {x & 1, y & 1, z & 1};
+    uint32_t c = 0, unit = 1;
+#pragma unroll
+    for (int axis = 0; axis < 3; axis++) {
+        if (nbr[(int64_t)(2 * axis + odd[axis]) * ld + i] >= 0) c += unit * (uint32_t)(1 + odd[axis]);
+        unit *= 3;
+    }
+    parent[i] = (uint32_t)rank_lookup(crank[p >> 5], (uint32_t)p) | c << kParentBits;
+}
+
+// A parent word's cell, and the slot of the outer neighbour of each axis (-1 absent).
+__device__ __forceinline__ int64_t mg_parent_cell(uint32_t w, int (&slot)[3]) {
+    const uint32_t c = w >> kParentBits;
+    const uint32_t s2 = (c * 57u) >> 9, r = c - 9u * s2, s1 = (r * 11u) >> 5, s0 = r - 3u * s1;   // c / 9, r / 3
+    slot[0] = (int)s0 - 1;
+    slot[1] = s1 ? 1 + (int)s1 : -1;
+    slot[2] = s2 ? 3 + (int)s2 : -1;
+    return (int64_t)(w & ((1u << kParentBits) - 1u));
 }
 
 // set-up: mass and face weights of the cells of level l + 1 from level l
@@ -407,35 +700,102 @@ __global__ __launch_bounds__(kBlock) void k_mg_invd(const float *__restrict__ w,
     invd[i] = 1.0 / ((double)mass[i] + a * s);
 }
 
-// Fine-level residual of the pre-smoothed iterate: t = r - B x0 (x0 = w D^-1 r,
-// written by the update kernel), one thread per voxel.
-template <bool REG, int NS>
-__global__ __launch_bounds__(kBlock) void k_mg_res0(CgArgs A, const double *__restrict__ r,
-                                                    const double *__restrict__ x0, double *__restrict__ t,
-                                                    const double *__restrict__ scal) {
+// Fine-level residual of the pre-smoothed iterate x0 = w D^-1 r, which is
+// formed in registers for the voxel and its neighbours: t = r - B x0, one
+// thread per voxel.  With rr_part, first the convergence check of iterate k
+// from its Gp residual partials.
+template <bool REG, int NS, int V>
+__global__ __launch_bounds__(kBlock) void k_mg_res0(CgArgs A, int k, const double *__restrict__ r,
+                                                    const double *__restrict__ m, double *__restrict__ t,
+                                                    double *__restrict__ scal,
+                                                    const double *__restrict__ rr_part, int Gp) {
     if (scal[S_DONE] != 0.0) return;
+    constexpr bool ST = V > 1;
+    __shared__ double win[ST ? 2 : 1][ST ? kCgWin : 1];
+    __shared__ double lds[kWaves];
     __shared__ double cl[VG_NREG];
+    __shared__ double mtab[8];
     if (threadIdx.x < VG_NREG) cl[threadIdx.x] = A.c[threadIdx.x];
+    if (!REG && threadIdx.x < 7) mtab[threadIdx.x] = 1.0 / (1.0 + A.a * (double)threadIdx.x);
     __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= A.n) return;
-    const double xi = x0[i];
-    int64_t j[6];
-    bool pres[6];
-    cg_neighbours<NS>(A, i, j, pres);
-    double xj[6];
+    if (rr_part && cg_check(rr_part, Gp, k, scal[S_BB], scal, lds)) return;
+    const int64_t nt = (A.n + kBlock * V - 1) / (kBlock * V);
+    int64_t tl = xcd_stride_tile(blockIdx.x, gridDim.x, 0, nt, A.run);
+    CgIdx<NS> i[V];
+    bool act[V];
+    CgWords<NS> w[V];
+    cg_own(A, tl, i, act);
 #pragma unroll
-    for (int k = 0; k < 6; k++) xj[k] = x0[j[k]];
-    double s = 0.0;
+    for (int v = 0; v < V; v++) cg_words<NS>(A, i[v], w[v]);
+    for (int64_t it = 1; tl < nt; it++) {
+        constexpr int K0 = ST ? 4 : 0;   // the slots gathered from memory
+        bool pres[V][6];
+        double ri[V], mi[V], xj[V][6], mj[V][6];
+        [[maybe_unused]] uint32_t q[V][4];
+        [[maybe_unused]] double hx[2], hm[2];
 #pragma unroll
-    for (int k = 0; k < 6; k++) {
-        if (!pres[k]) continue;
-        s += weight(A.rcode, cl, i, k, REG) * (xi - xj[k]);
+        for (int v = 0; v < V; v++) {
+            CgIdx<NS> j[6];
+            cg_decode<NS>(A, i[v], w[v], j, pres[v]);
+            ri[v] = el(r, i[v]);
+#pragma unroll
+            for (int k6 = K0; k6 < 6; k6++) xj[v][k6] = el(r, j[k6]);
+            mi[v] = fine_minv<REG>(m, mtab, i[v]);
+#pragma unroll
+            for (int k6 = K0; k6 < 6; k6++) mj[v][k6] = fine_minv<REG>(m, mtab, j[k6]);
+            if constexpr (ST) {
+#pragma unroll
+                for (int k4 = 0; k4 < 4; k4++) q[v][k4] = (uint32_t)(j[k4] - (uint32_t)(tl * V * kBlock)) + kCgHalo;
+            }
+        }
+        if constexpr (ST) {
+            uint32_t hi[2];
+            cg_halo(A, tl, hi);
+#pragma unroll
+            for (int u = 0; u < 2; u++) {
+                hx[u] = el(r, hi[u]);
+                hm[u] = fine_minv<REG>(m, mtab, hi[u]);
+            }
+        }
+        tl = xcd_stride_tile(blockIdx.x, gridDim.x, it, nt, A.run);
+        CgIdx<NS> in[V];
+        bool an[V];
+        cg_own(A, tl, in, an);
+#pragma unroll
+        for (int v = 0; v < V; v++) cg_words<NS>(A, in[v], w[v]);
+        double xi[V];
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            xi[v] = kMgOmega * ri[v] * mi[v];
+#pragma unroll
+            for (int k6 = K0; k6 < 6; k6++) xj[v][k6] = kMgOmega * xj[v][k6] * mj[v][k6];
+        }
+        if constexpr (ST) {
+#pragma unroll
+            for (int u = 0; u < 2; u++) hx[u] = kMgOmega * hx[u] * hm[u];
+            double *wb = win[it & 1];
+            cg_stage(wb, xi, hx);
+#pragma unroll
+            for (int v = 0; v < V; v++)
+#pragma unroll
+                for (int k4 = 0; k4 < 4; k4++) xj[v][k4] = wb[q[v][k4]];
+        }
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            double s = 0.0;
+#pragma unroll
+            for (int k6 = 0; k6 < 6; k6++) {
+                const double wt = weight(A.rcode, cl, i[v], k6, REG);
+                s += pres[v][k6] ? wt * (xi[v] - xj[v][k6]) : 0.0;
+            }
+            if (act[v]) el(t, i[v]) = ri[v] - (xi[v] + A.a * s);
+            i[v] = in[v];
+            act[v] = an[v];
+        }
     }
-    t[i] = r[i] - (xi + A.a * s);
 }
 
-// Residual on level l >= 1 (into e, free until the upward pass): r - B x.
+// Residual on level l >= 1 (into e): r - B x.
 __global__ __launch_bounds__(kBlock) void k_mg_res(MgView L, double a, const double *__restrict__ scal) {
     if (scal[S_DONE] != 0.0) return;
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -470,7 +830,7 @@ __global__ __launch_bounds__(kBlock) void k_mg_sum(const RankWord *__restrict__ 
 
 // The coarsest level (at most kMgCoarseMax cells): kMgSweeps damped Jacobi
 // sweeps from zero (the first is the x the restriction wrote) in one block,
-// the iterate in LDS; the result goes to e.
+// the iterate in LDS; the result replaces x.
 __global__ __launch_bounds__(kMgCoarseThreads) void k_mg_coarsest(MgView L, double a,
                                                                   const double *__restrict__ scal) {
     if (scal[S_DONE] != 0.0) return;
@@ -500,41 +860,52 @@ __global__ __launch_bounds__(kMgCoarseThreads) void k_mg_coarsest(MgView L, doub
     }
     for (int u = 0; u < kPer; u++) {
         const int64_t i = threadIdx.x + (int64_t)u * kMgCoarseThreads;
-        if (i < L.n) L.e[i] = xs[src][i];
+        if (i < L.n) L.x[i] = xs[src][i];
     }
 }
 
-// Prolongation: y = x + sol_c[parent] (any level; streaming).
-__global__ __launch_bounds__(kBlock) void k_mg_pro(int64_t n, const double *__restrict__ x,
-                                                   const int32_t *__restrict__ parent,
-                                                   const double *__restrict__ solc, double *__restrict__ y,
-                                                   const double *__restrict__ scal) {
-    if (scal[S_DONE] != 0.0) return;
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) y[i] = x[i] + solc[parent[i]];
+// The coarse solution's part of B P e at a cell: sum over the cell's outer
+// neighbours of w (e_I - e_J), I its parent and J the parent's neighbour on
+// that side.
+template <typename W>
+__device__ __forceinline__ double mg_outer(const int32_t *__restrict__ cnbr, int64_t cld,
+                                           const double *__restrict__ e, int64_t I, double eI, const int (&slot)[3],
+                                           W &&w) {
+    int64_t J[3];
+    double eJ[3];
+#pragma unroll
+    for (int axis = 0; axis < 3; axis++) J[axis] = slot[axis] >= 0 ? (int64_t)cnbr[(int64_t)slot[axis] * cld + I] : I;
+#pragma unroll
+    for (int axis = 0; axis < 3; axis++) eJ[axis] = e[J[axis]];
+    double s = 0.0;
+#pragma unroll
+    for (int axis = 0; axis < 3; axis++)
+        if (slot[axis] >= 0) s += w(slot[axis]) * (eI - eJ[axis]);
+    return s;
 }
 
-// Post-smoothing on level l >= 1: x = y + w D^-1 (r - B y), y in e.
-__global__ __launch_bounds__(kBlock) void k_mg_post(MgView L, double a, const double *__restrict__ scal) {
+// Prolongation and post-smoothing on level l >= 1 (see the top): x <- x +
+// P e + w D^-1 (t - B P e), t the residual in e, the coarse solution in C.x.
+__global__ __launch_bounds__(kBlock) void k_mg_post(MgView L, MgView C, double a, const double *__restrict__ scal) {
     if (scal[S_DONE] != 0.0) return;
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= L.n) return;
-    const double yi = L.e[i];
-    double s = 0.0;
-#pragma unroll
-    for (int k = 0; k < 6; k++) {
-        const int32_t j = L.nbr[(int64_t)k * L.ld + i];
-        if (j >= 0) s += (double)L.w[(int64_t)k * L.ld + i] * (yi - L.e[j]);
-    }
-    L.x[i] = yi + kMgOmega * (L.r[i] - ((double)L.mass[i] * yi + a * s)) * L.invd[i];
+    int slot[3];
+    const int64_t I = mg_parent_cell(L.parent[i], slot);
+    const double eI = C.x[I];
+    const double s = mg_outer(C.nbr, C.ld, C.x, I, eI, slot,
+                              [&](int q) { return (double)L.w[(int64_t)q * L.ld + i]; });
+    L.x[i] += eI + kMgOmega * (L.e[i] - ((double)L.mass[i] * eI + a * s)) * L.invd[i];
 }
 
-// Post-smoothing on the fine level: z = y + w D^-1 (r - B y), y in t; writes
-// z and the per-block r.z partials (slot 0, the grid-stride blocks of the
-// other CG kernels).
+// The same on the fine level, x = w D^-1 r formed from r (512^3: 178 us; as a
+// prolongation and a smoothing kernel that gathered the fine iterate 130 +
+// 170 us): writes z and the
+// per-block r.z partials (the grid-stride blocks of the other CG kernels).
 template <bool REG, int NS>
 __global__ __launch_bounds__(kBlock) void k_mg_post0(CgArgs A, const double *__restrict__ r,
-                                                     const double *__restrict__ m, const double *__restrict__ y,
+                                                     const double *__restrict__ m, const double *__restrict__ t,
+                                                     const uint32_t *__restrict__ parent, MgView C,
                                                      double *__restrict__ z, const double *__restrict__ scal,
                                                      double *__restrict__ part) {
     if (scal[S_DONE] != 0.0) return;
@@ -544,45 +915,48 @@ __global__ __launch_bounds__(kBlock) void k_mg_post0(CgArgs A, const double *__r
     if (threadIdx.x < VG_NREG) cl[threadIdx.x] = A.c[threadIdx.x];
     if (!REG && threadIdx.x < 7) mtab[threadIdx.x] = 1.0 / (1.0 + A.a * (double)threadIdx.x);
     __syncthreads();
+    constexpr int V = kMgPostV;
+    const int64_t nt = (A.n + kBlock * V - 1) / (kBlock * V);
     double acc[1] = {0.0};
-    for (int64_t it = 0;; it++) {
-    const int64_t t = xcd_stride_tile(blockIdx.x, gridDim.x, it, A.ntiles);
-    if (t >= A.ntiles) break;
-    for (int v = 0; v < kVPT; v++) {
-        const int64_t i = t * kTile + v * kBlock + threadIdx.x;
-        if (i >= A.n) continue;
-        const double yi = y[i];
-        int64_t j[6];
-        bool pres[6];
-        cg_neighbours<NS>(A, i, j, pres);
-        double yj[6];
+    int64_t tl = xcd_stride_tile(blockIdx.x, gridDim.x, 0, nt, A.run);
+    CgIdx<NS> i[V];
+    uint32_t pw[V];
+    bool act[V];
+    cg_own(A, tl, i, act);
 #pragma unroll
-        for (int k = 0; k < 6; k++) yj[k] = y[j[k]];
-        const double ri = r[i], mi = fine_minv<REG>(m, mtab, i);
-        double s = 0.0;
+    for (int v = 0; v < V; v++) pw[v] = el(parent, i[v]);
+    for (int64_t it = 1; tl < nt; it++) {
+        double ri[V], ti[V], mi[V], eI[V], s[V];
 #pragma unroll
-        for (int k = 0; k < 6; k++) {
-            if (!pres[k]) continue;
-            s += weight(A.rcode, cl, i, k, REG) * (yi - yj[k]);
+        for (int v = 0; v < V; v++) {
+            ri[v] = el(r, i[v]);
+            ti[v] = el(t, i[v]);
+            mi[v] = fine_minv<REG>(m, mtab, i[v]);
+            int slot[3];
+            const int64_t I = mg_parent_cell(pw[v], slot);
+            eI[v] = C.x[I];
+            s[v] = mg_outer(C.nbr, C.ld, C.x, I, eI[v], slot,
+                            [&](int q) { return weight(A.rcode, cl, i[v], q, REG); });
         }
-        const double zi = yi + kMgOmega * (ri - (yi + A.a * s)) * mi;
-        z[i] = zi;
-        acc[0] += ri * zi;
-    }
+        tl = xcd_stride_tile(blockIdx.x, gridDim.x, it, nt, A.run);
+        CgIdx<NS> in[V];
+        bool an[V];
+        cg_own(A, tl, in, an);
+#pragma unroll
+        for (int v = 0; v < V; v++) pw[v] = el(parent, in[v]);
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            const double zi = kMgOmega * ri[v] * mi[v] + eI[v] + kMgOmega * (ti[v] - (eI[v] + A.a * s[v])) * mi[v];
+            if (act[v]) {
+                el(z, i[v]) = zi;
+                acc[0] += ri[v] * zi;
+            }
+            i[v] = in[v];
+            act[v] = an[v];
+        }
     }
     block_sum<1>(acc, lds);
-    if (threadIdx.x == 0) part[(int64_t)blockIdx.x * 4] = acc[0];
-}
-
-// The pre-smoothed fine iterate for a given r (vg_precondition): x0 = w D^-1 r.
-template <bool REG>
-__global__ __launch_bounds__(kBlock) void k_mg_x0(int64_t n, double a, const double *__restrict__ r,
-                                                  const double *__restrict__ m, double *__restrict__ x0) {
-    __shared__ double mtab[8];
-    if (!REG && threadIdx.x < 7) mtab[threadIdx.x] = 1.0 / (1.0 + a * (double)threadIdx.x);
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) x0[i] = kMgOmega * r[i] * fine_minv<REG>(m, mtab, i);
+    if (threadIdx.x == 0) part[P_RZ * A.ldp + (int)blockIdx.x] = acc[0];
 }
 
 // Jacobi as a separate map (vg_precondition): z = D^-1 r.
@@ -642,7 +1016,7 @@ Geom fine_geom(const vg_sim *h) {
     return g;
 }
 
-CgArgs cg_args(const vg_sim *h, double a) {
+CgArgs cg_args(const vg_sim *h, double a, int V = 1) {
     CgArgs A;
     A.nbr = h->nbr;
     A.rcode = h->rcode;
@@ -650,6 +1024,8 @@ CgArgs cg_args(const vg_sim *h, double a) {
     A.n = h->n;
     A.ntiles = h->ntiles;
     A.a = a;
+    A.ldp = h->cg_blocks;
+    A.run = xcd_run(h, V);
     for (int k = 0; k < VG_NREG; k++) A.c[k] = h->c[k];
     return A;
 }
@@ -693,18 +1069,31 @@ int mg_prepare(vg_sim *h, double a, hipStream_t s) {
     return VG_OK;
 }
 
-// z = V-cycle(r) on the fine level: z holds x0 = w D^-1 r on entry (the
-// update or init kernel wrote it), m the fine diagonal as the init kernel
-// wrote it; r.z partials go to part slot 0 of G blocks.  Each level's
-// result: x (levels between), e (the coarsest).
+// Blocks of a grid-stride kernel over the voxels, V per thread: as many as
+// are resident, no more than there is work for, within the partials.
+int cg_grid(const vg_sim *h, const void *kernel, int V) {
+    const int64_t nt = (h->n + kBlock * V - 1) / (kBlock * V);
+    return resident_blocks(kernel, (int)(nt < h->cg_blocks ? nt : h->cg_blocks));
+}
+
 template <bool REG, int NS>
-int mg_vcycle(vg_sim *h, const CgArgs &A, const double *r, const double *m, double *z, int G, hipStream_t s) {
+int mg_rz_blocks(const vg_sim *h) {
+    return cg_grid(h, (const void *)k_mg_post0<REG, NS>, kMgPostV);
+}
+
+// z = V-cycle(r) on the fine level, m the fine diagonal as the init kernel
+// wrote it; the r.z partials go to slot P_RZ (mg_rz_blocks of them).  Each
+// level's result is in x.  Gp > 0: the first kernel also checks the
+// convergence of iterate k from its Gp residual partials.
+template <bool REG, int NS, int V>
+int mg_vcycle(vg_sim *h, const CgArgs &A, int k, int Gp, const double *r, const double *m, double *z,
+              hipStream_t s) {
     const int L = h->mg_levels;
     const double a = A.a;
-    double *t = h->mg[0].e;   // fine residual, then the prolongated iterate
+    double *t = h->mg[0].e;   // fine residual
     int rc;
-    hipLaunchKernelGGL((k_mg_res0<REG, NS>), dim3(mg_grid(h->n)), dim3(kBlock), 0, s, A, r, (const double *)z, t,
-                       h->cg_scal);
+    hipLaunchKernelGGL((k_mg_res0<REG, NS, V>), dim3(cg_grid(h, (const void *)k_mg_res0<REG, NS, V>, V)), dim3(kBlock), 0, s, A,
+                       k, r, m, t, h->cg_scal, Gp > 0 ? (const double *)h->cg_part + P_RR * A.ldp : nullptr, Gp);
     if ((rc = launch_status("k_mg_res0"))) return rc;
     hipLaunchKernelGGL(k_mg_sum, dim3(mg_grid(h->mg[1].n)), dim3(kBlock), 0, s, (const RankWord *)h->rank,
                        fine_geom(h), (const double *)t, mg_view(h, 1), h->cg_scal);
@@ -720,19 +1109,13 @@ int mg_vcycle(vg_sim *h, const CgArgs &A, const double *r, const double *m, doub
     hipLaunchKernelGGL(k_mg_coarsest, dim3(1), dim3(kMgCoarseThreads), 0, s, mg_view(h, L - 1), a, h->cg_scal);
     if ((rc = launch_status("k_mg_coarsest"))) return rc;
     for (int l = L - 2; l >= 1; l--) {
-        const MgView V = mg_view(h, l);
-        const double *solc = l + 1 == L - 1 ? h->mg[l + 1].e : h->mg[l + 1].x;
-        hipLaunchKernelGGL(k_mg_pro, dim3(mg_grid(V.n)), dim3(kBlock), 0, s, V.n, (const double *)V.x, V.parent,
-                           solc, V.e, h->cg_scal);
-        if ((rc = launch_status("k_mg_pro"))) return rc;
-        hipLaunchKernelGGL(k_mg_post, dim3(mg_grid(V.n)), dim3(kBlock), 0, s, V, a, h->cg_scal);
+        hipLaunchKernelGGL(k_mg_post, dim3(mg_grid(h->mg[l].n)), dim3(kBlock), 0, s, mg_view(h, l), mg_view(h, l + 1),
+                           a, h->cg_scal);
         if ((rc = launch_status("k_mg_post"))) return rc;
     }
-    const double *sol1 = L == 2 ? h->mg[1].e : h->mg[1].x;
-    hipLaunchKernelGGL(k_mg_pro, dim3(mg_grid(h->n)), dim3(kBlock), 0, s, h->n, (const double *)z,
-                       (const int32_t *)h->mg[0].parent, sol1, t, h->cg_scal);
-    if ((rc = launch_status("k_mg_pro"))) return rc;
-    hipLaunchKernelGGL((k_mg_post0<REG, NS>), dim3(G), dim3(kBlock), 0, s, A, r, m, (const double *)t, z, h->cg_scal,
+    hipLaunchKernelGGL((k_mg_post0<REG, NS>), dim3(mg_rz_blocks<REG, NS>(h)), dim3(kBlock), 0, s,
+                       cg_args(h, a, kMgPostV), r, m, (const double *)t,
+                       (const uint32_t *)h->mg[0].parent, mg_view(h, 1), z, h->cg_scal,
                        h->cg_part);
     return launch_status("k_mg_post0");
 }
@@ -753,72 +1136,94 @@ CompAcc pool_acc<CompAcc>(vg_sim *h, int pool) {
     return CompAcc{(float *)h->fields + (int64_t)pool * h->n, h->lo + (int64_t)pool * h->n};
 }
 
-template <typename F, int NS, bool REG, bool MG>
+template <typename F, int NS, bool REG, bool MG, int V>
 int cg_solve_t(vg_sim *h, int pool, double a, double rtol, int max_iter, int *iters, double *relres,
                hipStream_t s) {
-    const CgArgs A = cg_args(h, a);
-    const int G = h->cg_blocks;
+    const CgArgs A = cg_args(h, a, V);
+    const int Gi = cg_grid(h, (const void *)k_cg_init<F, REG, NS, MG>, 1);
+    const int Gd = cg_grid(h, (const void *)k_cg_dot<REG, NS, MG, V>, V);
+    const int Gs = cg_grid(h, (const void *)k_cg_step<REG, NS, MG, V>, V);
     const F field = pool_acc<F>(h, pool);
     int rc;
     // squared tolerance (compared with squared norms; rtol^2 is exact enough)
-    double host_scal[S_NSCAL] = {0, 0, 0, 0, 0, 0, 0, rtol * rtol};
+    double host_scal[S_NSCAL] = {};
+    host_scal[S_RTOL2] = rtol * rtol;
     if ((rc = hip_status(hipMemcpyAsync(h->cg_scal, host_scal, sizeof(host_scal), hipMemcpyHostToDevice, s),
                          "cg scalars"))) return rc;
     if (MG && (rc = mg_prepare(h, a, s))) return rc;
-    hipLaunchKernelGGL((k_cg_init<F, REG, NS, MG>), dim3(G), dim3(kBlock), 0, s, A, field, h->cg_y, h->cg_r, h->cg_z,
-                       h->cg_p[0], h->cg_m, h->cg_part, h->cg_q);
+    // Jacobi: z ping-pongs (iterate k in zb[k & 1]); MG: z and r
+    double *zb[2] = {h->cg_z, MG ? h->cg_z : h->cg_r};
+    hipLaunchKernelGGL((k_cg_init<F, REG, NS, MG>), dim3(Gi), dim3(kBlock), 0, s, A, field, h->cg_y,
+                       MG ? h->cg_r : zb[0], h->cg_m, h->cg_part);
     if ((rc = launch_status("k_cg_init"))) return rc;
-    if (MG && (rc = mg_vcycle<REG, NS>(h, A, h->cg_r, h->cg_m, h->cg_z, G, s))) return rc;
-    hipLaunchKernelGGL(k_cg_scalars, dim3(1), dim3(kBlock), 0, s, h->cg_part, G, 0, h->cg_scal);
-    if ((rc = launch_status("k_cg_scalars"))) return rc;
+    hipLaunchKernelGGL(k_cg_status, dim3(1), dim3(kBlock), 0, s, A.ldp, Gi, 0, h->cg_scal, (const double *)h->cg_part);
+    if ((rc = launch_status("k_cg_status"))) return rc;
+    if (MG && (rc = mg_vcycle<REG, NS, V>(h, A, 0, 0, h->cg_r, h->cg_m, h->cg_z, s))) return rc;
 
-    int launched = 0, cur = 0;
-    const int chunk = 8;
-    double back[S_NSCAL];
+    int launched = 0, todo = 8;
+    double back[S_NSCAL], rr0 = 0.0;
+    int it0 = 0;
     for (;;) {
+        if (launched > 0) {
+            hipLaunchKernelGGL(k_cg_status, dim3(1), dim3(kBlock), 0, s, A.ldp, Gs, launched, h->cg_scal,
+                               (const double *)h->cg_part);
+            if ((rc = launch_status("k_cg_status"))) return rc;
+        }
         if ((rc = hip_status(hipMemcpyAsync(back, h->cg_scal, sizeof(back), hipMemcpyDeviceToHost, s),
                              "cg scalars back"))) return rc;
         if ((rc = hip_status(hipStreamSynchronize(s), "cg sync"))) return rc;
         if (back[S_DONE] != 0.0 || launched >= max_iter) break;
-        const int todo = (max_iter - launched) < chunk ? (max_iter - launched) : chunk;
+        // the next batch: the iterations the convergence so far says are
+        // left (kernels past convergence cost a few microseconds each, a
+        // host round trip more than that)
+        if (launched > 0 && back[S_RR] < rr0 && back[S_RTOL2] * back[S_BB] > 0.0) {
+            const double per = (__builtin_log(rr0) - __builtin_log(back[S_RR])) / (double)(launched - it0);
+            const double left = (__builtin_log(back[S_RR]) - __builtin_log(back[S_RTOL2] * back[S_BB])) / per;
+            todo = left < 2.0 ? 2 : (left < 32.0 ? (int)left + 1 : 32);
+        } else {
+            todo = 8;
+        }
+        rr0 = back[S_RR];
+        it0 = launched;
+        if (todo > max_iter - launched) todo = max_iter - launched;
         for (int it = 0; it < todo; it++) {
-            hipLaunchKernelGGL((k_cg_spmv<REG, NS>), dim3(G), dim3(kBlock), 0, s, A, h->cg_z, h->cg_p[cur],
-                               h->cg_p[cur ^ 1], h->cg_y, h->cg_q, h->cg_scal, h->cg_part);
-            if ((rc = launch_status("k_cg_spmv"))) return rc;
-            hipLaunchKernelGGL(k_cg_scalars, dim3(1), dim3(kBlock), 0, s, h->cg_part, G, 1, h->cg_scal);
-            if ((rc = launch_status("k_cg_scalars"))) return rc;
-            hipLaunchKernelGGL((k_cg_update<REG, MG>), dim3(G), dim3(kBlock), 0, s, h->n, h->ntiles, a, h->cg_q,
-                               h->cg_m, h->cg_r, h->cg_z, h->cg_scal, h->cg_part);
-            if ((rc = launch_status("k_cg_update"))) return rc;
-            if (MG && (rc = mg_vcycle<REG, NS>(h, A, h->cg_r, h->cg_m, h->cg_z, G, s))) return rc;
-            hipLaunchKernelGGL(k_cg_scalars, dim3(1), dim3(kBlock), 0, s, h->cg_part, G, 2, h->cg_scal);
-            if ((rc = launch_status("k_cg_scalars"))) return rc;
-            cur ^= 1;   // p ping-pong (iteration k writes p[k & 1]); after convergence the kernels return early
+            const int k = launched + it;
+            hipLaunchKernelGGL((k_cg_dot<REG, NS, MG, V>), dim3(Gd), dim3(kBlock), 0, s, A, k,
+                               MG ? mg_rz_blocks<REG, NS>(h) : (k > 0 ? Gs : Gi), (const double *)zb[k & 1], h->cg_scal, h->cg_part);
+            if ((rc = launch_status("k_cg_dot"))) return rc;
+            hipLaunchKernelGGL((k_cg_step<REG, NS, MG, V>), dim3(Gs), dim3(kBlock), 0, s, A, k, Gd,
+                               (const double *)zb[k & 1], (const double *)h->cg_p[(k & 1) ^ 1], h->cg_p[k & 1], h->cg_y,
+                               MG ? h->cg_r : zb[(k & 1) ^ 1], h->cg_scal, h->cg_part);
+            if ((rc = launch_status("k_cg_step"))) return rc;
+            if (MG && (rc = mg_vcycle<REG, NS, V>(h, A, k + 1, Gs, h->cg_r, h->cg_m, h->cg_z, s))) return rc;
         }
         launched += todo;
     }
+    // direction k is in p[k & 1]; after an odd number of iterations the last one (even k) is still to add
+    const int done = (int)back[S_ITER];
     hipLaunchKernelGGL((k_cg_writeback<F>), dim3((unsigned)((h->n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                       h->n, h->cg_y, h->cg_p[(int)back[S_ITER] & 1], h->cg_scal, field);
+                       h->n, (const double *)h->cg_y, (const double *)h->cg_p[0], done & 1,
+                       (const double *)h->cg_scal, field);
     if ((rc = launch_status("k_cg_writeback"))) return rc;
-    if (iters) *iters = (int)back[S_ITER];
+    if (iters) *iters = done;
     if (relres) *relres = back[S_BB] > 0.0 ? __builtin_sqrt(back[S_RR] / back[S_BB]) : 0.0;
     return back[S_DONE] != 0.0 ? VG_OK : VG_ENOCONV;
 }
 
-template <typename F, int NS>
+template <typename F, int NS, int V>
 int cg_solve_ns(vg_sim *h, int pool, double a, double rtol, int max_iter, int *iters, double *relres,
                 hipStream_t s) {
     const bool reg = h->rcode != nullptr;
     const bool mg = h->precond == VG_PRECOND_MG && h->mg_levels >= 2;
-    if (reg) return mg ? cg_solve_t<F, NS, true, true>(h, pool, a, rtol, max_iter, iters, relres, s)
-                       : cg_solve_t<F, NS, true, false>(h, pool, a, rtol, max_iter, iters, relres, s);
-    return mg ? cg_solve_t<F, NS, false, true>(h, pool, a, rtol, max_iter, iters, relres, s)
-              : cg_solve_t<F, NS, false, false>(h, pool, a, rtol, max_iter, iters, relres, s);
+    if (reg) return mg ? cg_solve_t<F, NS, true, true, V>(h, pool, a, rtol, max_iter, iters, relres, s)
+                       : cg_solve_t<F, NS, true, false, V>(h, pool, a, rtol, max_iter, iters, relres, s);
+    return mg ? cg_solve_t<F, NS, false, true, V>(h, pool, a, rtol, max_iter, iters, relres, s)
+              : cg_solve_t<F, NS, false, false, V>(h, pool, a, rtol, max_iter, iters, relres, s);
 }
 
-template <int NS>
+template <int NS, int V>
 int mg_apply_ns(vg_sim *h, double a, const double *r, double *z, hipStream_t s) {
-    const CgArgs A = cg_args(h, a);
+    const CgArgs A = cg_args(h, a, V);
     const bool reg = h->rcode != nullptr;
     const bool mg = h->precond == VG_PRECOND_MG && h->mg_levels >= 2;
     int rc;
@@ -833,20 +1238,28 @@ int mg_apply_ns(vg_sim *h, double a, const double *r, double *z, hipStream_t s) 
     // the V-cycle's kernels check the convergence flag: clear it
     if ((rc = hip_status(hipMemsetAsync(h->cg_scal, 0, sizeof(double) * S_NSCAL, s), "cg scalars"))) return rc;
     if ((rc = mg_prepare(h, a, s))) return rc;
-    if (reg) hipLaunchKernelGGL(k_mg_x0<true>, dim3(mg_grid(h->n)), dim3(kBlock), 0, s, h->n, a, r, h->cg_m, z);
-    else hipLaunchKernelGGL(k_mg_x0<false>, dim3(mg_grid(h->n)), dim3(kBlock), 0, s, h->n, a, r, h->cg_m, z);
-    if ((rc = launch_status("k_mg_x0"))) return rc;
-    return reg ? mg_vcycle<true, NS>(h, A, r, h->cg_m, z, h->cg_blocks, s)
-               : mg_vcycle<false, NS>(h, A, r, h->cg_m, z, h->cg_blocks, s);
+    return reg ? mg_vcycle<true, NS, V>(h, A, 0, 0, r, h->cg_m, z, s)
+               : mg_vcycle<false, NS, V>(h, A, 0, 0, r, h->cg_m, z, s);
 }
 
-// the explicit step's neighbour source
+// The explicit step's neighbour source, but the table where the FP64 vectors
+// outgrow the packed sources' 32-bit byte offsets (the fields may be FP32).
+bool cg_packed(const vg_sim *h) { return (uint64_t)h->n * sizeof(double) < ((uint64_t)1 << 32); }
+
+// The staged kernels: relative codes, x and y distances within the halo, and
+// enough voxels (see kCgTileV).
+bool cg_staged(const vg_sim *h) {
+    return use_relative(h) && h->xy_dist >= 0 && h->xy_dist <= kCgHalo && h->n >= kCgStagedMin;
+}
+
 template <typename F>
 int cg_solve(vg_sim *h, int pool, double a, double rtol, int max_iter, int *iters, double *relres,
              hipStream_t s) {
-    if (use_relative(h)) return cg_solve_ns<F, NS_REL>(h, pool, a, rtol, max_iter, iters, relres, s);
-    if (use_offsets(h)) return cg_solve_ns<F, NS_OFF>(h, pool, a, rtol, max_iter, iters, relres, s);
-    return cg_solve_ns<F, NS_TABLE>(h, pool, a, rtol, max_iter, iters, relres, s);
+    if (!cg_packed(h)) return cg_solve_ns<F, NS_TABLE, 1>(h, pool, a, rtol, max_iter, iters, relres, s);
+    if (cg_staged(h)) return cg_solve_ns<F, NS_REL, kCgTileV>(h, pool, a, rtol, max_iter, iters, relres, s);
+    if (use_relative(h)) return cg_solve_ns<F, NS_REL, 1>(h, pool, a, rtol, max_iter, iters, relres, s);
+    if (use_offsets(h)) return cg_solve_ns<F, NS_OFF, 1>(h, pool, a, rtol, max_iter, iters, relres, s);
+    return cg_solve_ns<F, NS_TABLE, 1>(h, pool, a, rtol, max_iter, iters, relres, s);
 }
 
 }  // namespace
@@ -882,7 +1295,7 @@ int mg_build(vg_sim *h, hipStream_t s) {
         if (l > 0 && F.n <= kMgCoarsest) break;
         vg_sim::MgLevel &C = h->mg[l + 1];
         const int32_t *fvox = l == 0 ? h->vox : F.vox;
-        int32_t *fparent = l == 0 ? h->mg[0].parent : F.parent;
+        uint32_t *fparent = F.parent;
         const size_t cells = (size_t)C.nx * C.ny * C.nz;
         if ((rc = hip_status(hipMemsetAsync(h->mg_mask, 0, cells, s), "clear occupancy"))) return rc;
         hipLaunchKernelGGL(k_mg_mark, dim3(mg_grid(F.n)), dim3(kBlock), 0, s, fvox, F.n, F.nx, F.ny, C.nx, C.ny,
@@ -896,7 +1309,8 @@ int mg_build(vg_sim *h, hipStream_t s) {
         Geom cg;
         make_geom(C.nx, C.ny, C.nz, 0, &cg);
         hipLaunchKernelGGL(k_mg_parent, dim3(mg_grid(F.n)), dim3(kBlock), 0, s, fvox, F.n, F.nx, F.ny,
-                           (const RankWord *)C.rank, cg, fparent);
+                           (const RankWord *)C.rank, cg, l == 0 ? h->nbr : (const int32_t *)F.nbr,
+                           l == 0 ? h->n : F.cap, fparent);
         if ((rc = launch_status("k_mg_parent"))) return rc;
         l++;
     }
@@ -910,9 +1324,11 @@ int mg_build(vg_sim *h, hipStream_t s) {
 
 int mg_apply(vg_sim *h, double a, const double *r, double *z, hipStream_t s) {
     if (h->n == 0) return VG_OK;
-    if (use_relative(h)) return mg_apply_ns<NS_REL>(h, a, r, z, s);
-    if (use_offsets(h)) return mg_apply_ns<NS_OFF>(h, a, r, z, s);
-    return mg_apply_ns<NS_TABLE>(h, a, r, z, s);
+    if (!cg_packed(h)) return mg_apply_ns<NS_TABLE, 1>(h, a, r, z, s);
+    if (cg_staged(h)) return mg_apply_ns<NS_REL, kCgTileV>(h, a, r, z, s);
+    if (use_relative(h)) return mg_apply_ns<NS_REL, 1>(h, a, r, z, s);
+    if (use_offsets(h)) return mg_apply_ns<NS_OFF, 1>(h, a, r, z, s);
+    return mg_apply_ns<NS_TABLE, 1>(h, a, r, z, s);
 }
 
 int run_cg(vg_sim *h, int pool, double a, double rtol, int max_iter, int *iters, double *relres,

@@ -95,22 +95,24 @@ __device__ inline int64_t xcd_tile(int64_t b, int64_t nb) {
 
 // Tile of iteration `it` of block b in a grid-stride kernel of nb blocks.
 // With nb a multiple of 8 the blocks of one XCD (b % 8) walk that XCD's own
-// runs of kXcdRun consecutive tiles (the runs xcd_tile deals to it), then
-// its contiguous share of the tiles after the last full round of runs, so a
-// grid-stride kernel keeps the locality of the one-tile-per-block kernels;
-// otherwise plain striding.  Returns ntiles once the block's list is done.
-__device__ inline int64_t xcd_stride_tile(int64_t b, int64_t nb, int64_t it, int64_t ntiles) {
+// runs of S consecutive tiles (runs dealt to the XCDs in turn, as in
+// xcd_tile), then its contiguous share of the tiles after the last full round
+// of runs, so a grid-stride kernel keeps the locality of the
+// one-tile-per-block kernels; otherwise plain striding.  Returns ntiles once
+// the block's list is done.  (Tiles number fewer than 2^31 / kBlock.)
+__device__ inline int64_t xcd_stride_tile(int64_t b, int64_t nb, int64_t it, int64_t ntiles,
+                                          uint32_t S = (uint32_t)kXcdRun) {
     if (nb % kNumXcd != 0) {
         const int64_t t = b + it * nb;
         return t < ntiles ? t : ntiles;
     }
-    constexpr int64_t S = kXcdRun, R = S * kNumXcd;
-    const int64_t x = b % kNumXcd, m = it * (nb / kNumXcd) + b / kNumXcd;
-    const int64_t nfull = ntiles / R * R, own_full = nfull / kNumXcd;
+    const uint32_t R = S * (uint32_t)kNumXcd;
+    const uint32_t x = (uint32_t)b % kNumXcd, m = (uint32_t)it * ((uint32_t)nb / kNumXcd) + (uint32_t)b / kNumXcd;
+    const uint32_t nfull = (uint32_t)ntiles / R * R, own_full = nfull / kNumXcd;
     if (m < own_full) return ((m / S) * kNumXcd + x) * S + m % S;
-    const int64_t u = m - own_full, tail = ntiles - nfull;
-    const int64_t q = tail / kNumXcd, r = tail % kNumXcd;
-    if (u >= q + (x < r ? 1 : 0)) return ntiles;
+    const uint32_t u = m - own_full, tail = (uint32_t)ntiles - nfull;
+    const uint32_t q = tail / kNumXcd, r = tail % kNumXcd;
+    if (u >= q + (x < r ? 1u : 0u)) return ntiles;
     return nfull + x * q + (x < r ? x : r) + u;
 }
 
@@ -465,6 +467,34 @@ __device__ __forceinline__ void packed_decode(const PackedNbr &P, uint32_t i, Pa
     }
 }
 
+// The same for gathers of many lanes at once: for an absent neighbour a
+// valid index near the ones the lanes beside it load (with relative codes the
+// group's base distance away), and its slot's bit in the result clear.
+template <bool RELC>
+__device__ __forceinline__ uint32_t packed_decode_near(const PackedNbr &P, uint32_t i, uint32_t n, PackedWords W,
+                                                       uint32_t (&j)[6]) {
+    uint32_t pres = 0;
+    if (RELC) {
+        const uint32_t grp = __builtin_amdgcn_readfirstlane(i / (uint32_t)kGroup);
+        const uint32_t *bp = P.rel_base + (size_t)grp * 8;
+        uint32_t base[6];
+#pragma unroll
+        for (int k = 0; k < 6; k++) base[k] = bp[k];
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            const uint32_t c = (W.a >> P.rl.sh[k]) & P.rl.mk[k];
+            const uint32_t d = base[k] + (c ? c - 1u : 0u);
+            j[k] = (k & 1) ? min(i + d, n - 1u) : i - min(d, i);
+            pres |= c ? 1u << k : 0u;
+        }
+    } else {
+        packed_decode<false>(P, i, W, j);
+#pragma unroll
+        for (int k = 0; k < 6; k++) pres |= j[k] != i ? 1u << k : 0u;
+    }
+    return pres;
+}
+
 }  // namespace vg
 
 // ---------------------------------------------------------------- handle
@@ -509,6 +539,8 @@ struct vg_sim {
     uint32_t *off_m = nullptr, *off_p = nullptr;   // [n] each
     uint32_t *off_stat = nullptr;                  // [8] max offset per axis, violation flag, code spans
     bool off_ok = false;
+    // largest |i - j| of x and y neighbours and of z neighbours; -1 unknown or across a periodic wrap
+    int64_t xy_dist = -1, z_dist = -1;
     vg::DLayout off_layout;
     // relative neighbour codes (4 B per voxel plus 32 B per 64 voxels)
     uint32_t *rel_w = nullptr;      // [n]
@@ -530,9 +562,9 @@ struct vg_sim {
     int part_slot = 0;           // the slot the next pass with totals writes
     double *tot_tmp = nullptr;   // [nseg][6]
     // implicit CG (FP64 vectors)
-    double *cg_y = nullptr, *cg_r = nullptr, *cg_z = nullptr, *cg_q = nullptr, *cg_m = nullptr;
+    double *cg_y = nullptr, *cg_r = nullptr, *cg_z = nullptr, *cg_m = nullptr;
     double *cg_p[2] = {nullptr, nullptr};
-    double *cg_part = nullptr;   // [cg_blocks][4]
+    double *cg_part = nullptr;   // [4][cg_blocks]
     double *cg_scal = nullptr;   // scalars (see vg_cg.hip)
     int cg_blocks = 0;
     // multigrid preconditioner of the CG (VG_FEAT_MG; vg_cg.hip).  Level 0 is
@@ -545,7 +577,7 @@ struct vg_sim {
         float *w = nullptr;              // [6][cap] edge weights, 0 if absent (levels >= 1)
         float *mass = nullptr;           // [cap] voxels in the cell (levels >= 1)
         double *invd = nullptr, *r = nullptr, *x = nullptr, *e = nullptr;   // [cap] (levels >= 1)
-        int32_t *parent = nullptr;       // [cap] cell of the next level (all but the coarsest)
+        uint32_t *parent = nullptr;      // [cap] cell of the next level and outer neighbours (k_mg_parent; all but the coarsest)
         vg::RankWord *rank = nullptr;    // rank index of the grid (levels >= 1; level 0 uses the handle's)
     };
     MgLevel mg[VG_MG_MAX_LEVELS];
@@ -579,6 +611,17 @@ struct vg_sim {
 };
 
 namespace vg {
+
+// Block tiles of V * kBlock voxels per XCD run of a grid-stride kernel that
+// gathers: an eighth of a plane (the distance of z neighbours in the compact
+// list), so that a tile's z neighbours were or will be read on the same XCD
+// and come from its L2 (conjugate gradients at 512^3: 4 % faster than runs
+// of 64 tiles).
+inline uint32_t xcd_run(const vg_sim *h, int V) {
+    if (h->z_dist <= 0) return (uint32_t)kXcdRun;
+    const int64_t unit = (int64_t)kNumXcd * kBlock * V, r = (h->z_dist + unit / 2) / unit;
+    return (uint32_t)(r < 1 ? 1 : r);
+}
 
 // launchers (vg_step.hip)
 enum { MODE_T = 0, MODE_D = 1, MODE_DT = 2, MODE_NONE = 3 };

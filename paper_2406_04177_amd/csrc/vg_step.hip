@@ -414,9 +414,9 @@ __global__ __launch_bounds__(kBlock) void k_step_off(StepBufs<R> B, Coef<R> C, P
         for (int s = 0; s < VG_NPOOL; s++)
             x[v][s] = reads<MODE, MOB, TOT>(s) ? (mobile<MOB>(s) ? at(B.src[s], ic[v]) : ld_once(&at(B.src[s], ic[v])))
                                                : R(0);
-    uint32_t j[V][6];
+    uint32_t j[V][6], pres[V];
 #pragma unroll
-    for (int v = 0; v < V; v++) packed_decode<RELC>(B.pk, ic[v], pw[v], j[v]);   // lanes past n hold n - 1
+    for (int v = 0; v < V; v++) pres[v] = packed_decode_near<RELC>(B.pk, ic[v], n, pw[v], j[v]);   // lanes past n hold n - 1
     R w[V][6];
 #pragma unroll
     for (int v = 0; v < V; v++) {
@@ -452,7 +452,10 @@ __global__ __launch_bounds__(kBlock) void k_step_off(StepBufs<R> B, Coef<R> C, P
             const R xi = x[v][s];
             R d[6];
 #pragma unroll
-            for (int k = 0; k < 6; k++) d[k] = REG ? w[v][k] * (g[v][m][k] - xi) : g[v][m][k] - xi;
+            for (int k = 0; k < 6; k++) {
+                const R gk = ((pres[v] >> k) & 1u) ? g[v][m][k] : xi;
+                d[k] = REG ? w[v][k] * (gk - xi) : gk - xi;
+            }
             const R sum = ((d[0] + d[1]) + (d[2] + d[3])) + (d[4] + d[5]);
             x[v][s] = xi + C.a[s] * sum;
         }
@@ -1461,6 +1464,7 @@ static uint32_t bit_width(uint32_t v) {
 int build_offsets(vg_sim *h, hipStream_t s) {
     h->off_ok = false;
     h->rel_ok = false;
+    h->xy_dist = h->z_dist = -1;
     if (h->n == 0 || !h->off_m || !h->rel_w || !h->nbr) return VG_OK;
     int rc;
     if ((rc = hip_status(hipMemsetAsync(h->off_stat, 0, 8 * sizeof(uint32_t), s), "clear offset statistics")))
@@ -1474,6 +1478,10 @@ int build_offsets(vg_sim *h, hipStream_t s) {
     if ((rc = hip_status(hipMemcpyAsync(st, h->off_stat, sizeof(st), hipMemcpyDeviceToHost, s), "read offsets")))
         return rc;
     if ((rc = hip_status(hipStreamSynchronize(s), "synchronise"))) return rc;
+    if (!st[3]) {
+        h->xy_dist = st[0] > st[1] ? st[0] : st[1];
+        h->z_dist = st[2];
+    }
     const uint32_t bx = bit_width(st[0]), by = bit_width(st[1]), bz = bit_width(st[2]);
     // periodic wrap or byte offsets beyond 32 bits: neither packing
     if (st[3] || (uint64_t)h->n * h->elem() >= ((uint64_t)1 << 32)) return VG_OK;
