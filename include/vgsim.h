@@ -310,16 +310,17 @@ int vg_destroy(vg_sim *h);
 #define VG_KERNEL_RANK     2
 #define VG_KERNEL_OFFSET   3
 #define VG_KERNEL_RELATIVE 4
-/* VG_KERNEL_BAND: RELATIVE codes, and runs of four consecutive fused passes
- * (steps with no totals logged) as two launches of a kernel that applies two
+/* VG_KERNEL_BAND: RELATIVE codes, and consecutive fused passes (steps with no
+ * totals logged) in pairs, each one launch of a kernel that applies two
  * fused passes (Scheme 1 diffusion, then Algorithm 1, twice) to bands of
  * rows marching along z: the intermediate DOM of a band, its neighbour rows
  * and the planes next to it stay in LDS, so a pass pair reads and writes the
  * fields once.  Needs the workspace of VG_FEAT_BAND and the relative codes;
  * used while only DOM diffuses, with unit edge weights (no region codes) and
  * Algorithm 1; other passes run on RELATIVE.  Bit-identical to RELATIVE.
- * AUTO takes BAND for FP32 fields when it is available and the volume has
- * enough planes for chunks of at least 20 (about 512^3 and up). */
+ * AUTO takes BAND for FP32 and FP64 fields when it is available and the
+ * volume has enough planes for chunks of at least 8 (about 300^3 and up in
+ * FP32, 220^3 in FP64). */
 #define VG_KERNEL_BAND     5
 int vg_set_kernel(vg_sim *h, int variant);
 

@@ -1,6 +1,7 @@
 // C-ABI of libvgsim: handle, argument validation, workspace layout and the
 // orchestration of the kernels of vg_step.hip, vg_cg.hip and vg_adjoint.hip.
 // Owns no device memory: every device buffer is bound by the caller.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -375,12 +376,13 @@ int launch_run(vg_sim *h, double dt, bool band, hipStream_t s) {
                              "begin capture")))
             return rc;
         int lrc = VG_OK;
-        for (int64_t k = 0; k < kRunPasses && lrc == VG_OK; k += band ? 4 : 1)
-            lrc = band ? launch_band_quad(h, dt, h->capture_stream)
+        for (int64_t k = 0; k < kRunPasses && lrc == VG_OK; k += band ? 2 : 1)
+            lrc = band ? launch_band_pair(h, dt, h->capture_stream)
                        : launch_pass(h, MODE_DT, TOT_NONE, dt, h->capture_stream);
         hipGraph_t graph = nullptr;
         rc = hip_status(hipStreamEndCapture(h->capture_stream, &graph), "end capture");
         h->cur = cur0;   // capturing ran nothing
+        h->band_mid = 0;
         if (lrc || rc) {
             if (graph) (void)hipGraphDestroy(graph);
             return lrc ? lrc : rc;
@@ -553,6 +555,7 @@ extern "C" int vg_step_explicit(vg_sim *h, int64_t nsteps, double dt, int64_t lo
     if ((rc = need_bound(h))) return rc;
     if (nsteps == 0 || h->n == 0) return VG_OK;
     hipStream_t s = (hipStream_t)stream;
+    h->band_mid = 0;
     const size_t row = (size_t)h->nseg * 6;
     auto logged = [&](int64_t j) { return log_every > 0 && j % log_every == 0; };
     // the partials of up to tot_batch logged passes wait in their slots and
@@ -570,15 +573,32 @@ extern "C" int vg_step_explicit(vg_sim *h, int64_t nsteps, double dt, int64_t lo
         if (++h->part_slot < h->tot_batch) return VG_OK;
         return flush();
     };
-    // four fused passes j .. j + 3 with no totals logged run as two band
-    // launches when the band kernel applies
+    // fused passes with no totals logged run in pairs on the band kernel
+    // where it applies; each launch moves the state to the other field set,
+    // and a single fused pass can take it back
     const bool band = use_band(h);
     auto quiet = [&](int64_t j, int64_t last, int64_t len) {
         if (j + len - 1 > last) return false;
         if (log_every > 0 && (j + log_every - 1) / log_every * log_every <= j + len - 1) return false;
         return true;
     };
-    auto quiet4 = [&](int64_t j, int64_t last) { return band && quiet(j, last, 4); };
+    // band launches from pass j on: as many pairs as there are quiet passes
+    // for, but an even number where no single fused pass follows
+    auto pairs_at = [&](int64_t j, int64_t last) -> int64_t {
+        if (!band) return 0;
+        int64_t len = last - j + 1;
+        if (log_every > 0) len = std::min(len, (j + log_every - 1) / log_every * log_every - j);
+        int64_t pairs = len / 2;
+        if (len % 2 == 0 && j + len > last) pairs -= pairs % 2;
+        return pairs;
+    };
+    auto run_pairs = [&](int64_t pairs) -> int {
+        for (int64_t q = 0; q < pairs; q++) {
+            const int rc2 = launch_band_pair(h, dt, s);
+            if (rc2) return rc2;
+        }
+        return VG_OK;
+    };
     // longer quiet runs are replayed from a captured graph
     const bool graphs = graphs_wanted(h);
     auto quiet_run = [&](int64_t j, int64_t last) { return graphs && quiet(j, last, kRunPasses); };
@@ -590,10 +610,10 @@ extern "C" int vg_step_explicit(vg_sim *h, int64_t nsteps, double dt, int64_t lo
                 j += kRunPasses - 1;
                 continue;
             }
-            if (quiet4(j, nsteps - 1)) {
-                if ((rc = launch_band_quad(h, dt, s))) return rc;
-                j += 3;
-                continue;
+            if (const int64_t pairs = pairs_at(j, nsteps - 1); pairs > 0) {
+                if ((rc = run_pairs(pairs))) return rc;
+                j += 2 * pairs;
+                if (j > nsteps - 1) break;
             }
             const bool lg = logged(j);
             if ((rc = launch_pass(h, MODE_DT, lg ? TOT_MID : TOT_NONE, dt, s))) return rc;
@@ -609,10 +629,10 @@ extern "C" int vg_step_explicit(vg_sim *h, int64_t nsteps, double dt, int64_t lo
                 j += kRunPasses - 1;
                 continue;
             }
-            if (quiet4(j, nsteps)) {
-                if ((rc = launch_band_quad(h, dt, s))) return rc;
-                j += 3;
-                continue;
+            if (const int64_t pairs = pairs_at(j, nsteps); pairs > 0) {
+                if ((rc = run_pairs(pairs))) return rc;
+                j += 2 * pairs;
+                if (j > nsteps) break;
             }
             const bool lg = logged(j);
             if ((rc = launch_pass(h, MODE_DT, lg ? TOT_OUT : TOT_NONE, dt, s))) return rc;

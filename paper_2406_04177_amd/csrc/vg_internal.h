@@ -549,10 +549,12 @@ struct vg_sim {
     vg::RLayout rel_layout;
     // two-pass band kernel (single raster volume; see vg_step.hip)
     int32_t *band_rs = nullptr;     // [nz * ny + 1] compact index of the first voxel of each row
-    char *band_alt = nullptr;       // [5][n] field type: the pass pair's intermediate fields
+    char *band_alt = nullptr;       // [5][n] field type: the second field set of the pass pairs
+    int band_mid = 0;               // the state is in band_alt (only within a run of passes)
     bool band_ok = false;           // built and fits the LDS
     bool band_auto = false;         // chunks long enough for AUTO to take it
-    int band_h = 0, band_z = 0, band_nbands = 0, band_nchunks = 0, band_cap = 0;
+    int band_h = 0, band_z = 0, band_nbands = 0;
+    int64_t band_capf = 0, band_cape = 0;   // widest ranges of a plane (BandGeom)
     std::vector<int32_t> piece_first_h, piece_seg_h, seg_first_h;
     std::vector<int64_t> piece_lo_h;
     int32_t *piece_first = nullptr, *piece_seg = nullptr, *seg_first = nullptr;
@@ -649,7 +651,7 @@ int tape_rows(const vg_sim *h);        // rows per recorded state: 4 with the ke
 void tape_pass_bufs(const vg_sim *h, void *states, int64_t j, const void *src[VG_NPOOL], void *dst[VG_NPOOL],
                     void **xdom);
 int build_band(vg_sim *h, hipStream_t s);
-int launch_band_quad(vg_sim *h, double dt, hipStream_t s);
+int launch_band_pair(vg_sim *h, double dt, hipStream_t s);
 PackedNbr packed_of(const vg_sim *h);
 int build_offsets(vg_sim *h, hipStream_t s);
 int restore_canonical(vg_sim *h, hipStream_t s);

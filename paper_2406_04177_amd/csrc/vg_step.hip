@@ -34,6 +34,8 @@
 // transform), so n paper steps run as T, K^(n-1), D.  Inside a K pass the
 // state between its D and T halves is exactly the paper state after a full
 // step, which is where the totals of that step are taken.
+#include <algorithm>
+
 #include "vg_internal.h"
 
 #pragma clang fp contract(off)
@@ -1025,17 +1027,25 @@ int dispatch_bufs(vg_sim *h, int mode, int tot, double dt_t, double dt_d, const 
 // [y0, y0 + H) of the planes [z0, z0 + Z) and marches along z.  At plane p
 // it applies the first pass to the rows [y0 - 1, y0 + H] (the band and one
 // neighbour row on each side: one contiguous range of the compact list) and
-// keeps in LDS the DOM of those rows after the first pass (three planes) and
-// after its diffusion (two planes).  Then it applies the second pass to the
-// band rows of plane p - 1: every neighbour's first-pass DOM is in LDS (same
-// plane: band and neighbour rows; planes p - 2 and p: band rows); the other
-// first-pass pools are recomputed from the input pools and the diffused DOM.
-// The output is written once per pass pair.  Inputs and outputs are separate
-// field sets, since neighbouring blocks read the inputs next to their rows
-// and planes.  Same operations in the same order as two single passes, so
-// the result is bit-identical.
+// the second pass to the band rows of plane p - 1.  LDS rings hold the DOM
+// before the first pass (rows [y0 - 2, y0 + H + 1], four planes) and after
+// it (four planes), so that every neighbour of both passes is an LDS read;
+// what else the second pass needs of a voxel (the other pools after the
+// first pass, its code) stays in the registers of the thread that computed
+// it.  So every load of the kernel is a contiguous stream whose address only
+// needs the row index: a plane's pools and codes are loaded while the plane
+// before it is computed, its DOM two planes ahead, and one barrier per plane
+// suffices.  Inputs and outputs are separate field sets, since neighbouring
+// blocks read the inputs next to their rows and planes.  Same operations in
+// the same order as two single passes, so the result is bit-identical.
+// (A gather of 64 lanes costs the vector cache up to 26 accesses where a
+// contiguous load costs 4, and a pass that gathers waits for the codes
+// first; the kernel before this one gathered the first pass's neighbours,
+// read the pools twice and took 388 us for a pass pair of 512^3 FP32, the
+// single passes 2 x 200.)
 struct BandGeom {
-    int ny, nz, H, Z, nbands, cap;   // cap: the widest range of a plane's band and neighbour rows
+    int ny, nz, H, Z, nbands;   // H rows and Z planes per block
+    uint32_t capf, cape;   // widest ranges of a plane: band and two / one neighbour rows on each side
 };
 
 // rs[r] = compact index of the first pore voxel at or after the start of
@@ -1054,162 +1064,228 @@ __global__ __launch_bounds__(kBlock) void k_band_rows(const int32_t *__restrict_
     rs[r] = (int32_t)lo;
 }
 
-// LDS of a block: [3][cap] DOM after the first pass, [2][cap] DOM after the
-// first pass's diffusion.
+// Threads and slots per thread: a plane's range with one neighbour row on
+// each side has at most kBandSlots voxels counted from the 64-voxel group it
+// starts in.  (The rows' pore counts vary twofold, so the slots are sized by
+// the widest plane and those past a plane's range are skipped.  Measured on
+// the 512^3 FP32 and a 331x257x403 FP64 call: 768 x 3 threads x slots 2.89
+// and 2.41 ms, 1024 x 2 3.69 and 2.41, 512 x 4 3.14 and 2.53; with the pools
+// loaded after the first pass instead of a plane ahead 3.28 and 2.79.)
+constexpr int kBandThreads = 768;
+constexpr int kBandU = 3;
+constexpr int kBandSlots = kBandThreads * kBandU;
+constexpr int kBandRaw = kBandU + 1;                       // loads per thread of a plane's DOM
+constexpr int kBandGroupWords = kBandSlots / kGroup * 8;   // base distances of a plane's groups
+
+// The two field sets of a launch.
 template <typename R>
-size_t band_lds_bytes(int cap) {
-    return (size_t)5 * cap * sizeof(R);
-}
-
-constexpr int kBandU = 4;   // slots per thread handled together: voxels base + u * kBlock + lane
-
-// First pass on U slots of plane p's range [es, ee); all loads of the slots
-// are issued before their use.
-template <typename R, int U>
-__device__ __forceinline__ void band_first(const StepBufs<R> &B, const Coef<R> &C, uint32_t base, uint32_t es,
-                                           uint32_t ee, R *d1, R *dm) {
-    const uint32_t lane = threadIdx.x & 63u;
-    uint32_t e[U], i[U], w[U];
-    R m[4][U];
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-        e[u] = base + (uint32_t)(u * kBlock) + lane;
-        i[u] = e[u] < es ? es : (e[u] < ee ? e[u] : ee - 1u);
-        w[u] = packed_words<true>(B.pk, i[u]).a;
-    }
-#pragma unroll
-    for (int u = 0; u < U; u++)
-#pragma unroll
-        for (int s = 0; s < 4; s++) m[s][u] = at(B.src[s], i[u]);   // CO2 does not enter the DOM
-    R g[U][6];
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-        uint32_t j[6];
-        packed_decode<true>(B.pk, i[u], PackedWords{w[u], 0u}, j);
-#pragma unroll
-        for (int k = 0; k < 6; k++) g[u][k] = at(B.src[1], j[k]);
-    }
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-        R x1 = m[0][u], x2 = m[1][u], x3 = m[2][u], x4 = m[3][u], x5 = R(0);
-        R d[6];
-#pragma unroll
-        for (int k = 0; k < 6; k++) d[k] = g[u][k] - x2;
-        x2 = x2 + C.a[1] * (((d[0] + d[1]) + (d[2] + d[3])) + (d[4] + d[5]));
-        const bool act = e[u] >= es && e[u] < ee;
-        if (act) dm[e[u] - es] = x2;
-        transform_alg<false>(C, x1, x2, x3, x4, x5);
-        if (act) d1[e[u] - es] = x2;
-    }
-}
-
-// Second pass on U slots of the band range [bs, be) of plane q: the pools
-// are read again and the first pass's transformation recomputed from its
-// diffused DOM; the neighbours' first-pass DOM comes from LDS.  In two
-// parts, so that the loads can be issued before the first pass of the same
-// marching step and their latency overlaps it.
-template <typename R, int U>
-struct BandSecond {
-    uint32_t e[U], i[U], w[U];
-    R m1[U], m3[U], m4[U], m5[U];
+struct BandBufs {
+    const R *src[VG_NPOOL];
+    R *dst[VG_NPOOL];
 };
 
-template <typename R, int U>
-__device__ __forceinline__ void band_second_load(const StepBufs<R> &B, uint32_t base, uint32_t bs, uint32_t be,
-                                                 BandSecond<R, U> &L) {
-    const uint32_t lane = threadIdx.x & 63u;
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-        L.e[u] = base + (uint32_t)(u * kBlock) + lane;
-        L.i[u] = L.e[u] < bs ? bs : (L.e[u] < be ? L.e[u] : be - 1u);
-        L.w[u] = packed_words<true>(B.pk, L.i[u]).a;
-        L.m1[u] = at(B.src[0], L.i[u]);
-        L.m3[u] = at(B.src[2], L.i[u]);
-        L.m4[u] = at(B.src[3], L.i[u]);
-        L.m5[u] = at(B.src[4], L.i[u]);
-    }
+// LDS of a block: [4][capf] DOM before, [4][cape] after the first pass, [4]
+// planes of base distances.
+template <typename R>
+size_t band_lds_bytes(int64_t capf, int64_t cape) {
+    return (size_t)4 * (size_t)(capf + cape) * sizeof(R) + (size_t)4 * kBandGroupWords * sizeof(uint32_t);
 }
 
-template <typename R, int U>
-__device__ __forceinline__ void band_second_finish(const StepBufs<R> &B, const Coef<R> &C, uint32_t base, uint32_t bs,
-                                                   uint32_t be, uint32_t es, uint32_t esm, uint32_t esp, const R *d1m,
-                                                   const R *d1c, const R *d1p, const R *dm, const BandSecond<R, U> &L) {
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-        if (base + (uint32_t)(u * kBlock) >= be) break;   // uniform over the wave
-        const uint32_t i = L.i[u];
-        R x1 = L.m1[u], x2 = dm[i - es], x3 = L.m3[u], x4 = L.m4[u], x5 = L.m5[u];
-        transform_alg<false>(C, x1, x2, x3, x4, x5);   // the first pass's output
-        uint32_t j[6];
-        packed_decode<true>(B.pk, i, PackedWords{L.w[u], 0u}, j);
-        R g[6];
-#pragma unroll
-        for (int k = 0; k < 4; k++) g[k] = d1c[j[k] - es];   // same plane (absent: i itself)
-        g[4] = j[4] == i ? x2 : d1m[j[4] - esm];
-        g[5] = j[5] == i ? x2 : d1p[j[5] - esp];
-        R d[6];
-#pragma unroll
-        for (int k = 0; k < 6; k++) d[k] = g[k] - x2;
-        x2 = x2 + C.a[1] * (((d[0] + d[1]) + (d[2] + d[3])) + (d[4] + d[5]));
-        transform_alg<false>(C, x1, x2, x3, x4, x5);
-        if (L.e[u] >= bs && L.e[u] < be) {
-            at(B.dst[0], i) = x1;
-            at(B.dst[1], i) = x2;
-            at(B.dst[2], i) = x3;
-            at(B.dst[3], i) = x4;
-            at(B.dst[4], i) = x5;
-        }
-    }
-}
+// Compact ranges of a plane's rows: the band (b), with one (e) and two (f)
+// neighbour rows on each side; empty outside the volume.
+struct BandRange {
+    uint32_t fs, fe, es, ee, bs, be;
+};
 
 template <typename R>
-__global__ __launch_bounds__(kBlock) void k_band2(StepBufs<R> B, Coef<R> C, BandGeom G,
-                                                  const int32_t *__restrict__ rs) {
+__global__ __launch_bounds__(kBandThreads) void k_band2(BandBufs<R> F, const uint32_t *__restrict__ rel_w,
+                                                        const uint32_t *__restrict__ rel_base, RLayout L, Coef<R> C,
+                                                        BandGeom G, const int32_t *__restrict__ rs) {
     extern __shared__ __align__(16) unsigned char band_lds[];
-    R *dom1 = reinterpret_cast<R *>(band_lds);
-    R *dmid = dom1 + 3 * G.cap;
-    const int band = (int)(blockIdx.x % (unsigned)G.nbands), chunk = (int)(blockIdx.x / (unsigned)G.nbands);
+    R *raw = reinterpret_cast<R *>(band_lds);
+    R *dom1 = raw + 4 * G.capf;
+    uint32_t *bas = reinterpret_cast<uint32_t *>(dom1 + 4 * G.cape);
+    constexpr int U = kBandU, NT = kBandThreads;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wb0 = __builtin_amdgcn_readfirstlane(tid & ~63u);   // the wave's first voxel of a slot
+    const int blk = (int)xcd_split(blockIdx.x, gridDim.x);      // neighbouring bands on one XCD
+    const int band = blk % G.nbands, chunk = blk / G.nbands;
     const int y0 = band * G.H, y1 = min(y0 + G.H, G.ny);
     const int ey0 = max(y0 - 1, 0), ey1 = min(y1 + 1, G.ny);
+    const int fy0 = max(y0 - 2, 0), fy1 = min(y1 + 2, G.ny);
     const int z0 = chunk * G.Z, z1 = min(z0 + G.Z, G.nz);
-    const uint32_t wave = threadIdx.x >> 6;
-    constexpr uint32_t kStep = (uint32_t)(kBandU * kBlock);
-    for (int p = z0 - 1; p <= z1; p++) {
-        // the second pass of this step works on plane q = p - 1, band rows:
-        // its first slots' pools and codes are loaded before the first pass
-        const int q = p - 1;
-        const int64_t rq = (int64_t)q * G.ny;
-        const bool has_q = q >= z0 && q < z1;
-        const uint32_t qbs = has_q ? (uint32_t)rs[rq + y0] : 0u, qbe = has_q ? (uint32_t)rs[rq + y1] : 0u;
-        const uint32_t qbase = (qbs & ~63u) + wave * 64u;
-        BandSecond<R, kBandU> L2;
-        if (qbs < qbe && qbase < qbe) band_second_load<R, kBandU>(B, qbase, qbs, qbe, L2);
-        // first pass on plane p, rows ey0 .. ey1 - 1 (waves start on 64-voxel
-        // groups: the relative codes' bases are per group)
-        const bool has_p = p >= 0 && p < G.nz;
-        const int64_t rp = (int64_t)p * G.ny;
-        const uint32_t es = has_p ? (uint32_t)rs[rp + ey0] : 0u, ee = has_p ? (uint32_t)rs[rp + ey1] : 0u;
-        if (es < ee) {   // plane p exists and its rows hold voxels
-            R *d1 = dom1 + ((p + 3) % 3) * G.cap, *dm = dmid + ((p + 2) % 2) * G.cap;
-            for (uint32_t base = (es & ~63u) + wave * 64u; base < ee; base += kStep)
-                band_first<R, kBandU>(B, C, base, es, ee, d1, dm);
+    auto range = [&](int p) {
+        BandRange r{0, 0, 0, 0, 0, 0};
+        if (p >= 0 && p < G.nz) {
+            const int32_t *row = rs + (int64_t)p * G.ny;
+            r.fs = (uint32_t)row[fy0];
+            r.fe = (uint32_t)row[fy1];
+            r.es = (uint32_t)row[ey0];
+            r.ee = (uint32_t)row[ey1];
+            r.bs = (uint32_t)row[y0];
+            r.be = (uint32_t)row[y1];
+            if (r.es == r.ee) r.es = r.ee = 0;   // no voxels: no slot is taken
         }
-        lds_barrier();
-        // second pass on plane q, band rows
-        if (qbs < qbe) {   // plane q is the block's and its band rows hold voxels
-            const uint32_t qes = (uint32_t)rs[rq + ey0];
-            const uint32_t esm = q > 0 ? (uint32_t)rs[rq - G.ny + ey0] : 0u;
-            const uint32_t esp = q + 1 < G.nz ? (uint32_t)rs[rq + G.ny + ey0] : 0u;
-            const R *d1m = dom1 + ((q + 2) % 3) * G.cap, *d1c = dom1 + ((q + 3) % 3) * G.cap,
-                    *d1p = dom1 + ((q + 4) % 3) * G.cap, *dmq = dmid + ((q + 2) % 2) * G.cap;
-            if (qbase < qbe) band_second_finish<R, kBandU>(B, C, qbase, qbs, qbe, qes, esm, esp, d1m, d1c, d1p, dmq, L2);
-            for (uint32_t base = qbase + kStep; base < qbe; base += kStep) {
-                BandSecond<R, kBandU> L;
-                band_second_load<R, kBandU>(B, base, qbs, qbe, L);
-                band_second_finish<R, kBandU>(B, C, base, qbs, qbe, qes, esm, esp, d1m, d1c, d1p, dmq, L);
+        return r;
+    };
+    // the DOM of a plane's f range: thread t's voxels fs + t, fs + NT + t, ...
+    auto load_raw = [&](const BandRange &r, R (&v)[kBandRaw]) {
+#pragma unroll
+        for (int k = 0; k < kBandRaw; k++) {
+            const uint32_t w0 = r.fs + wb0 + (uint32_t)(k * NT);
+            if (w0 < r.fe) v[k] = at(F.src[1], min(w0 + lane, r.fe - 1u));   // uniform over the wave
+        }
+    };
+    auto put_raw = [&](int p, const BandRange &r, const R (&v)[kBandRaw]) {
+        R *d = raw + (uint32_t)(p & 3) * G.capf;
+#pragma unroll
+        for (int k = 0; k < kBandRaw; k++) {
+            const uint32_t q0 = wb0 + (uint32_t)(k * NT), m = r.fe - r.fs;
+            if (q0 < m) d[min(q0 + lane, m - 1u)] = v[k];   // (lanes past the end hold the last value)
+        }
+    };
+    // base distances (less one) of the groups the e range touches, one word
+    // per thread, the y and z slots' first (one 16-byte read)
+    static_assert(kBandGroupWords <= NT, "one word per thread");
+    auto load_bas = [&](const BandRange &r) -> uint32_t {
+        const uint32_t g0 = r.es / kGroup * 8u, ng = r.ee > r.es ? (r.ee - 1u) / kGroup * 8u + 8u - g0 : 0u;
+        return tid < ng ? rel_base[g0 + tid] - 1u : 0u;
+    };
+    const uint32_t bpos = (tid & ~7u) | ((tid + 6u) & 7u);
+    auto put_bas = [&](int p, uint32_t v) {
+        if (tid < (uint32_t)kBandGroupWords) bas[(uint32_t)(p & 3) * kBandGroupWords + bpos] = v;
+    };
+    // a thread's slots of a plane: voxel e = first + u * NT, clamped to the range
+    // (the pools of the second pass are the first pass's results, in place)
+    struct Slots {
+        R m1[U], m3[U], m4[U], m5[U];
+        uint32_t w[U];
+    };
+    auto load_slots = [&](const BandRange &r, Slots &s) {
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const uint32_t wb = (r.es & ~63u) + wb0 + (uint32_t)(u * NT);
+            if (wb < r.ee) {   // uniform over the wave
+                const uint32_t e = wb + lane, i = e < r.es ? r.es : (e < r.ee ? e : r.ee - 1u);
+                s.w[u] = at(rel_w, i);
+                s.m1[u] = at(F.src[0], i);
+                s.m3[u] = at(F.src[2], i);
+                s.m4[u] = at(F.src[3], i);
+                s.m5[u] = at(F.src[4], i);
             }
         }
+    };
+    // LDS offsets (in elements of a ring) of the six neighbours of voxel i:
+    // own plane at oc - sc, below at om - sm, above at op - sp; an absent
+    // neighbour is the voxel itself
+    auto neighbours = [&](uint32_t w, const uint32_t *b, uint32_t i, uint32_t oc, uint32_t sc, uint32_t om,
+                          uint32_t sm, uint32_t op, uint32_t sp, uint32_t (&q)[6]) {
+        const uint32_t own = oc + (i - sc);
+        const uint4 bd = *reinterpret_cast<const uint4 *>(b);
+        uint32_t c[6];
+#pragma unroll
+        for (int k = 0; k < 6; k++) c[k] = (w >> L.sh[k]) & L.mk[k];
+        q[0] = own - c[0];   // raster order: an x neighbour is the voxel before or after (code 1)
+        q[1] = own + c[1];
+        const uint32_t ym = own - bd.x - c[2], yp = own + bd.y + c[3], zm = om + i - sm - bd.z - c[4],
+                       zp = op + i - sp + bd.w + c[5];
+        q[2] = c[2] ? ym : own;
+        q[3] = c[3] ? yp : own;
+        q[4] = c[4] ? zm : own;
+        q[5] = c[5] ? zp : own;
+    };
+
+    BandRange rm = range(z0 - 3), rq = range(z0 - 2), rp = range(z0 - 1), rn = range(z0), rn2 = range(z0 + 1);
+    (void)rm;
+    // march start: DOM of planes z0 - 2 .. z0, the first plane's slots
+    R v[kBandRaw];
+    {
+        R a0[kBandRaw], a1[kBandRaw];
+        load_raw(rq, a0);
+        load_raw(rp, a1);
+        load_raw(rn, v);
+        put_raw(z0 + 2, rq, a0);   // plane z0 - 2 (the ring position of z0 + 2)
+        put_raw(z0 + 3, rp, a1);
+        put_raw(z0, rn, v);
+    }
+    Slots nxt, cur, old;
+    load_slots(rp, nxt);
+    put_bas(z0 + 3, load_bas(rp));
+    load_raw(rn2, v);
+    uint32_t bv = load_bas(rn);
+    __syncthreads();
+    for (int p = z0 - 1; p <= z1; p++) {
+        const BandRange rn3 = range(p + 3);
+        cur = nxt;
+        if (p < z1) load_slots(rn, nxt);
+        // first pass on plane p, e range
+        const uint32_t fm = (uint32_t)((p + 3) & 3) * G.capf, fc = (uint32_t)(p & 3) * G.capf,
+                       fp = (uint32_t)((p + 1) & 3) * G.capf;
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const uint32_t wb = (rp.es & ~63u) + wb0 + (uint32_t)(u * NT);
+            if (wb < rp.ee) {
+                const uint32_t e = wb + lane, i = e < rp.es ? rp.es : (e < rp.ee ? e : rp.ee - 1u);
+                const uint32_t *bp = bas + (uint32_t)(p & 3) * kBandGroupWords + (wb / kGroup - rp.es / kGroup) * 8u;
+                uint32_t q[6];
+                neighbours(cur.w[u], bp, i, fc, rp.fs, fm, rq.fs, fp, rn.fs, q);
+                R x2 = raw[fc + (i - rp.fs)];
+                R g[6], d[6];
+#pragma unroll
+                for (int k = 0; k < 6; k++) g[k] = raw[q[k]];
+#pragma unroll
+                for (int k = 0; k < 6; k++) d[k] = g[k] - x2;
+                x2 = x2 + C.a[1] * (((d[0] + d[1]) + (d[2] + d[3])) + (d[4] + d[5]));
+                transform_alg<false>(C, cur.m1[u], x2, cur.m3[u], cur.m4[u], cur.m5[u]);
+                if (e >= rp.es && e < rp.ee) dom1[(uint32_t)(p & 3) * G.cape + (e - rp.es)] = x2;
+            }
+        }
+        if (p < z1) {
+            put_raw(p + 2, rn2, v);
+            put_bas(p + 1, bv);
+            load_raw(rn3, v);
+            bv = load_bas(rn2);
+        }
         lds_barrier();
+        // second pass on plane p - 1, band rows
+        if (p - 1 >= z0) {
+            const uint32_t dm = (uint32_t)((p + 2) & 3) * G.cape, dc = (uint32_t)((p + 3) & 3) * G.cape,
+                           dp = (uint32_t)(p & 3) * G.cape;
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const uint32_t wb = (rq.es & ~63u) + wb0 + (uint32_t)(u * NT);
+                if (wb < rq.be && wb + 64u > rq.bs) {
+                    const uint32_t e = wb + lane, i = e < rq.es ? rq.es : (e < rq.ee ? e : rq.ee - 1u);
+                    const uint32_t *bp =
+                        bas + (uint32_t)((p + 3) & 3) * kBandGroupWords + (wb / kGroup - rq.es / kGroup) * 8u;
+                    const bool act = e >= rq.bs && e < rq.be;
+                    // (the neighbour rows' outer neighbours are not held: lanes outside the band read the voxel itself)
+                    uint32_t q[6];
+                    neighbours(act ? old.w[u] : 0u, bp, i, dc, rq.es, dm, rm.es, dp, rp.es, q);
+                    R x1 = old.m1[u], x2 = dom1[dc + (i - rq.es)], x3 = old.m3[u], x4 = old.m4[u], x5 = old.m5[u];
+                    R g[6], d[6];
+#pragma unroll
+                    for (int k = 0; k < 6; k++) g[k] = dom1[q[k]];
+#pragma unroll
+                    for (int k = 0; k < 6; k++) d[k] = g[k] - x2;
+                    x2 = x2 + C.a[1] * (((d[0] + d[1]) + (d[2] + d[3])) + (d[4] + d[5]));
+                    transform_alg<false>(C, x1, x2, x3, x4, x5);
+                    if (act) {
+                        at(F.dst[0], i) = x1;
+                        at(F.dst[1], i) = x2;
+                        at(F.dst[2], i) = x3;
+                        at(F.dst[3], i) = x4;
+                        at(F.dst[4], i) = x5;
+                    }
+                }
+            }
+        }
+        old = cur;
+        rm = rq;
+        rq = rp;
+        rp = rn;
+        rn = rn2;
+        rn2 = rn3;
     }
 }
 
@@ -1306,6 +1382,15 @@ int dispatch(vg_sim *h, int mode, int tot, double dt_t, double dt_d, hipStream_t
         B.src[p] = cur;
         // a pass that diffuses writes mobile pools to the other buffer
         B.dst[p] = (mob_p && (mode == MODE_D || mode == MODE_DT)) ? oth : cur;
+        if (h->band_mid) {   // a fused pass that takes the state back from the band kernel's set
+            B.src[p] = (R *)h->band_alt + (int64_t)p * h->n;
+            B.dst[p] = cur;
+        }
+    }
+    if (h->band_mid) {
+        const int rc = dispatch_bufs<R>(h, mode, tot, dt_t, dt_d, B, s);
+        if (!rc) h->band_mid = 0;
+        return rc;
     }
     const int rc = dispatch_bufs<R>(h, mode, tot, dt_t, dt_d, B, s);
     if (rc) return rc;
@@ -1338,21 +1423,24 @@ bool band_geometry(const vg_sim *h) {
            h->periodic == 0 && h->n > 0 && h->prec != VG_F32C;
 }
 
-// AUTO takes the band kernel for FP32 fields when its chunks are long enough
-// (in FP64 its LDS budget allows only narrow bands: slower than single
-// passes).
+// AUTO takes the band kernel when its chunks are long enough (build_band).
 bool use_band(const vg_sim *h) {
     return h->band_ok && h->rel_ok && h->prec != VG_F32C &&
-           (h->kernel == VG_KERNEL_BAND || (h->kernel == VG_KERNEL_AUTO && h->prec == VG_F32 && h->band_auto)) &&
+           (h->kernel == VG_KERNEL_BAND || (h->kernel == VG_KERNEL_AUTO && h->band_auto)) &&
            !h->mobile_all && h->rcode == nullptr && h->params.sequential == 0;
 }
 
 // Row index, band height and chunk length.  The band height is the largest
-// of 8, 6, 4, 2 rows whose widest range of a plane's band and neighbour rows
-// fits a block's LDS budget (40 KiB); the chunks are sized so that every
-// block is resident at once.  Measured on the 512^3 FP32 step (a pass pair
-// in one launch vs two single passes): 8 rows 5.7 % faster, 6 rows equal,
-// 4 rows 23 % slower, 12 rows 3.5 % faster, 10 and 16 rows no faster.
+// whose widest plane fits the kernel's slots and whose LDS fits a CU, for
+// FP32 twice (taller bands recompute fewer neighbour rows; a march step costs
+// about 3 us whatever its width, so lower ones only add steps); the chunks
+// are sized so that every block is resident at once.
+// AUTO takes the kernel where the chunks have at least 8 planes: shorter ones
+// spend too much on their two extra planes.  Measured, 33 steps, single
+// passes over pairs: FP32 chunks of 4-6 planes (200^3, 256^3) 0.69-1.03, 8-9
+// (300^3; 500x120x500) 1.07-1.19, 24 and more (420^3 and up) 1.40-1.47; FP64
+// 6 planes (200^3) 0.99, 10-18 (256^3, 300^3) 1.13-1.29, 28 and more
+// 1.59-1.66.
 int build_band(vg_sim *h, hipStream_t s) {
     h->band_ok = false;
     h->band_auto = false;
@@ -1367,79 +1455,79 @@ int build_band(vg_sim *h, hipStream_t s) {
                          "band rows"))) return rc;
     if ((rc = hip_status(hipStreamSynchronize(s), "band rows"))) return rc;
     if (rs[(size_t)nrows] != h->n) { set_error("row index does not cover the compact list"); return VG_EINVAL; }
-    const size_t lds_max = 40 * 1024;
-    for (int H : {8, 6, 4, 2}) {
-        int64_t cap = 1;
-        for (int z = 0; z < h->nz; z++)
-            for (int y0 = 0; y0 < h->ny; y0 += H) {
-                const size_t r = (size_t)z * h->ny;
-                const int y1 = y0 + H < h->ny ? y0 + H : h->ny;
-                const int ey0 = y0 > 0 ? y0 - 1 : 0, ey1 = y1 + 1 < h->ny ? y1 + 1 : h->ny;
-                const int64_t c = (int64_t)rs[r + ey1] - rs[r + ey0];
-                if (c > cap) cap = c;
+    const size_t lds_cu = (size_t)160 * 1024;
+    static const int hs[] = {32, 28, 24, 20, 18, 16, 14, 12, 11, 10, 9, 8, 7, 6, 5, 4, 3, 2, 1};
+    for (size_t lds_max = h->prec == VG_F64 ? lds_cu : lds_cu / 2; lds_max <= lds_cu; lds_max *= 2) {
+        for (int H : hs) {
+            int64_t capf = 1, cape = 1;
+            bool fits = true;
+            for (int z = 0; z < h->nz && fits; z++)
+                for (int y0 = 0; y0 < h->ny; y0 += H) {
+                    const int32_t *row = rs.data() + (size_t)z * h->ny;
+                    const int y1 = std::min(y0 + H, h->ny);
+                    const int64_t es = row[std::max(y0 - 1, 0)], ee = row[std::min(y1 + 1, h->ny)];
+                    const int64_t f = (int64_t)row[std::min(y1 + 2, h->ny)] - row[std::max(y0 - 2, 0)];
+                    capf = std::max(capf, f);
+                    cape = std::max(cape, ee - es);
+                    if (ee - es / kGroup * kGroup > kBandSlots || f > (int64_t)kBandThreads * kBandRaw) {
+                        fits = false;
+                        break;
+                    }
+                }
+            if (!fits) continue;
+            const size_t lds = h->prec == VG_F64 ? band_lds_bytes<double>(capf, cape) : band_lds_bytes<float>(capf, cape);
+            if (lds > lds_max) continue;
+            h->band_h = H;
+            h->band_capf = capf;
+            h->band_cape = cape;
+            h->band_nbands = (h->ny + H - 1) / H;
+            // blocks resident at once (registers and this LDS size) on the device
+            int per = 0, cus = 0, dev = 0;
+            const void *kern = h->prec == VG_F64 ? (const void *)k_band2<double> : (const void *)k_band2<float>;
+            if (lds > 64 * 1024) (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max);
+            if (hipGetDevice(&dev) != hipSuccess ||
+                hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+                hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, kBandThreads, lds) != hipSuccess || per < 1) {
+                (void)hipGetLastError();
+                per = 2;
+                cus = 256;
             }
-        const size_t lds = h->prec == VG_F64 ? band_lds_bytes<double>((int)cap) : band_lds_bytes<float>((int)cap);
-        if (lds > lds_max) continue;
-        h->band_h = H;
-        h->band_cap = (int)cap;
-        h->band_nbands = (h->ny + H - 1) / H;
-        // blocks resident at once (registers and this LDS size) on the device
-        int per = 0, cus = 0, dev = 0;
-        const void *kern = h->prec == VG_F64 ? (const void *)k_band2<double> : (const void *)k_band2<float>;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, kBlock, lds) != hipSuccess || per < 1) {
-            (void)hipGetLastError();
-            per = 4;
-            cus = 256;
+            const int chunks = std::max(1, std::min(per * cus / h->band_nbands, (h->nz + 3) / 4));
+            h->band_z = (h->nz + chunks - 1) / chunks;
+            h->band_ok = true;
+            h->band_auto = h->band_z >= 8;
+            return VG_OK;
         }
-        const int resident = per * cus;
-        int chunks = (int)((resident + h->band_nbands / 2) / h->band_nbands);
-        if (chunks > (h->nz + 3) / 4) chunks = (h->nz + 3) / 4;
-        if (chunks < 1) chunks = 1;
-
-        h->band_z = (h->nz + chunks - 1) / chunks;
-        h->band_nchunks = (h->nz + h->band_z - 1) / h->band_z;
-        h->band_ok = true;
-        // AUTO leaves chunks of fewer than 20 planes to single passes: their
-        // two extra planes and the march's start cost more than the pass
-        // pair saves (256^3: 7-plane chunks, 47 % slower)
-        h->band_auto = h->band_z >= 20;
-        return VG_OK;
     }
     return VG_OK;
 }
 
 namespace {
 template <typename R>
-int band_quad(vg_sim *h, double dt, hipStream_t s) {
+int band_launch(vg_sim *h, double dt, hipStream_t s) {
     const Coef<R> C = make_coef2<R>(h, dt, dt);
-    BandGeom G{h->ny, h->nz, h->band_h, h->band_z, h->band_nbands, h->band_cap};
-    StepBufs<R> A = graph_bufs<R>(h), Bk = graph_bufs<R>(h);
-    R *canon = (R *)h->fields;
-    R *mid = (R *)h->band_alt;
+    const BandGeom G{h->ny, h->nz, h->band_h, h->band_z, h->band_nbands, (uint32_t)h->band_capf, (uint32_t)h->band_cape};
+    BandBufs<R> F;
     for (int p = 0; p < VG_NPOOL; p++) {
-        R *cur = (p == 1 && h->cur) ? (R *)h->alt : canon + (int64_t)p * h->n;
-        A.src[p] = cur;
-        A.dst[p] = mid + (int64_t)p * h->n;
-        Bk.src[p] = mid + (int64_t)p * h->n;
-        Bk.dst[p] = cur;
+        R *here = (p == 1 && h->cur) ? (R *)h->alt : (R *)h->fields + (int64_t)p * h->n;
+        R *mid = (R *)h->band_alt + (int64_t)p * h->n;
+        F.src[p] = h->band_mid ? mid : here;
+        F.dst[p] = h->band_mid ? here : mid;
     }
-    const unsigned grid = (unsigned)(h->band_nbands * h->band_nchunks);
-    const size_t lds = band_lds_bytes<R>(h->band_cap);
-    hipLaunchKernelGGL(k_band2<R>, dim3(grid), dim3(kBlock), lds, s, A, C, G, h->band_rs);
-    int rc = launch_status("k_band2");
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_band2<R>, dim3(grid), dim3(kBlock), lds, s, Bk, C, G, h->band_rs);
+    const int blocks = h->band_nbands * ((h->nz + h->band_z - 1) / h->band_z);
+    hipLaunchKernelGGL(k_band2<R>, dim3((unsigned)blocks), dim3(kBandThreads),
+                       band_lds_bytes<R>(h->band_capf, h->band_cape), s, F, (const uint32_t *)h->rel_w,
+                       (const uint32_t *)h->rel_base, h->rel_layout, C, G, (const int32_t *)h->band_rs);
     return launch_status("k_band2");
 }
 }  // namespace
 
-// Four fused passes as two band launches (into the intermediate field set
-// and back), so every pool ends where it started.
-int launch_band_quad(vg_sim *h, double dt, hipStream_t s) {
-    if (h->prec == VG_F64) return band_quad<double>(h, dt, s);
-    return band_quad<float>(h, dt, s);
+// Two fused passes: from where the state is (the bound fields, or the
+// intermediate set: h->band_mid) into the other set.
+int launch_band_pair(vg_sim *h, double dt, hipStream_t s) {
+    const int rc = h->prec == VG_F64 ? band_launch<double>(h, dt, s) : band_launch<float>(h, dt, s);
+    if (!rc) h->band_mid ^= 1;
+    return rc;
 }
 
 bool use_offsets(const vg_sim *h) {
