@@ -141,7 +141,7 @@ class _TotalsFn(torch.autograd.Function):
         dev = sim.fields.device
         n = sim.graph.n
         seeds = gout.detach().to(device=dev, dtype=torch.float64).contiguous()
-        lam = torch.zeros((5, n), dtype=sim.dtype, device=dev)
+        lam = torch.empty((5, n), dtype=sim.dtype, device=dev)      # the seed with zero=True writes every entry
         sim.seed_lambda(seeds[ctx.nsteps], lam, zero=True)
         grad = torch.zeros(NTHETA, dtype=torch.float64, device=dev)
         kmax = max((k for k0, k, _ in ctx.ckpts if k0 not in ctx.taped), default=0)

@@ -22,6 +22,7 @@
 // seeds of the totals are per volume): then the sweep carries it as one
 // value per volume (CO2U) and reads and writes 8 bytes less per voxel and
 // step; the per-voxel array is filled once at the end.
+#include <type_traits>
 #include <vector>
 
 #include "vg_internal.h"
@@ -232,6 +233,125 @@ __device__ __forceinline__ void adj_load_own(const AdjBufs<R> &A, const R *const
     if (REG) o.code = elem(A.rcode, i);
 }
 
+// The seeds of this step's totals and the uniform CO2 adjoint of voxel i64's
+// volume, taken piece by piece over the pieces that overlap its tile (uniform
+// loads): the last piece that starts at or before the voxel holds it.
+template <typename R, bool CO2U>
+__device__ __forceinline__ void adj_volume_terms(const AdjBufs<R> &A, const Pieces &pc, int64_t t, int64_t i64,
+                                                 double (&sd)[VG_NPOOL], R &lco2) {
+#pragma unroll
+    for (int s = 0; s < VG_NPOOL; s++) sd[s] = 0.0;
+    lco2 = R(0);
+    const int32_t pf = uload(pc.piece_first + t), pl = uload(pc.piece_first + t + 1);
+    for (int32_t p = pf; p < pl; p++) {
+        const int32_t sg = uload(pc.piece_seg + p);
+        const bool in = p == pf || i64 >= uload(pc.piece_lo + p);
+        const double *sp = A.seed + (int64_t)sg * VG_NPOOL;
+#pragma unroll
+        for (int s = 0; s < VG_NPOOL; s++) sd[s] = in ? uload(sp + s) : sd[s];
+        if (CO2U) lco2 = in ? uload(A.co2 + sg) : lco2;
+    }
+}
+
+// The reverse step at voxel i from its own words and neighbour values.  cl:
+// the region factors, creg: the block's region sums ([VG_NREG][kBlock], region
+// weights only), g: the thread's sums.
+template <typename R, int MOB, bool REG, bool FROM_X, int NS, bool DALL, bool CO2U>
+__device__ __forceinline__ void adj_voxel(const Coef<R> &C, const R *cl, double *creg, R *const *lout,
+                                          const AdjOwn<R, NS> &o, typename AdjIndex<NS>::T i,
+                                          const double (&sd)[VG_NPOOL], R lco2, const R (&zj)[VG_NPOOL][6],
+                                          const R (&lj)[VG_NPOOL][6], double (&g)[kG]) {
+    // forward state of this step and lambda^(k+1) of the voxel
+    R x[VG_NPOOL], li[VG_NPOOL];
+#pragma unroll
+    for (int s = 0; s < VG_NPOOL; s++) {
+        x[s] = o.x[s];
+        li[s] = o.li[s];
+    }
+    if (CO2U) li[4] = lco2;
+    R w[6];
+    uint32_t code = 0, own = 0;
+    if (REG) {
+        code = o.code;
+        own = code & 7u;
+        region_weights<R>(cl, code, w);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 6; k++) w[k] = R(1);
+    }
+    // x^k = D(z) of the stored z, with the forward's arithmetic
+    if (!FROM_X) {
+#pragma unroll
+        for (int s = 0; s < VG_NPOOL; s++) {
+            if (!mobile<MOB>(s)) continue;
+            const R xi = x[s];
+            R d[6];
+#pragma unroll
+            for (int k = 0; k < 6; k++) {
+                const R diff = zj[s][k] - xi;
+                d[k] = REG ? w[k] * diff : diff;
+            }
+            x[s] = xi + C.a[s] * (((d[0] + d[1]) + (d[2] + d[3])) + (d[4] + d[5]));
+        }
+    }
+    R u[VG_NPOOL] = {x[0], x[1], x[2], x[3], x[4]};
+    transform_fwd(C, u[0], u[1], u[2], u[3], u[4]);
+
+    // adjoint of the diffusion half: ubar = Q_w lambda; parameter terms
+    R bar[VG_NPOOL];
+    double own_c = 0.0, cross_c[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < VG_NPOOL; s++) {
+        if (!adj_differenced<MOB, DALL, CO2U>(s)) {
+            // (a uniform CO2 adjoint has no neighbour differences: its dL/dD term is 0)
+            bar[s] = li[s];
+            continue;
+        }
+        R sum = R(0);
+        // the voxel's terms of dw/dc (half of each cross-octant edge to
+        // each side), summed in the field type
+        R creg_own = R(0), creg_x[3] = {R(0), R(0), R(0)};
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            const R dl = lj[s][k] - li[s];
+            sum += w[k] * dl;
+            if (REG && mobile<MOB>(s)) {
+                if ((code >> (3 + k)) & 1u) {
+                    creg_own += R(0.5) * dl;
+                    creg_x[k >> 1] += R(0.5) * dl;
+                } else {
+                    creg_own += dl;
+                }
+            }
+        }
+        bar[s] = mobile<MOB>(s) ? li[s] + C.a[s] * sum : li[s];
+        g[s] += (double)(u[s] * sum);   // dL/da_s (each voxel's term in the field type)
+        if (REG && mobile<MOB>(s)) {
+            const R f = C.a[s] * u[s];
+            own_c += (double)(f * creg_own);
+            cross_c[0] += (double)(f * creg_x[0]);
+            cross_c[1] += (double)(f * creg_x[1]);
+            cross_c[2] += (double)(f * creg_x[2]);
+        }
+    }
+    if (REG) {
+        // four region slots of this thread (the octant and its three
+        // neighbours across the mid-planes); private, in a fixed order
+        const unsigned tid = threadIdx.x;
+        creg[own * kBlock + tid] += own_c;
+        if (__any(cross_c[0] != 0.0 || cross_c[1] != 0.0 || cross_c[2] != 0.0)) {   // few waves are at a mid-plane
+            creg[(own ^ 1u) * kBlock + tid] += cross_c[0];
+            creg[(own ^ 2u) * kBlock + tid] += cross_c[1];
+            creg[(own ^ 4u) * kBlock + tid] += cross_c[2];
+        }
+    }
+    // adjoint of the transformation half
+    transform_rev(C, x, bar, &g[5]);
+#pragma unroll
+    for (int s = 0; s < VG_NPOOL - 1; s++) elem(lout[s], i) = (R)((double)bar[s] + sd[s]);
+    if (!CO2U) elem(lout[4], i) = (R)((double)bar[4] + sd[4]);
+}
+
 // DALL: dL/da_s also for the pools that do not diffuse (their adjoints'
 // neighbour differences are gathered only for that term).
 template <typename R, int MOB, bool REG, bool FROM_X, int NS, bool DALL, bool CO2U>
@@ -271,24 +391,6 @@ __global__ __launch_bounds__(kBlock) void k_adj(AdjBufs<R> A, Coef<R> C, Pieces 
         lout[s] = A.lout + (int64_t)s * n;
     }
 
-    // the seeds of this step's totals and the uniform CO2 adjoint of voxel
-    // i64's volume, taken piece by piece over the pieces that overlap its
-    // tile (uniform loads): the last piece that starts at or before the
-    // voxel holds it
-    auto volume_terms = [&](int64_t t, int64_t i64, double (&sd)[VG_NPOOL], R &lco2) {
-#pragma unroll
-        for (int s = 0; s < VG_NPOOL; s++) sd[s] = 0.0;
-        lco2 = R(0);
-        const int32_t pf = uload(pc.piece_first + t), pl = uload(pc.piece_first + t + 1);
-        for (int32_t p = pf; p < pl; p++) {
-            const int32_t sg = uload(pc.piece_seg + p);
-            const bool in = p == pf || i64 >= uload(pc.piece_lo + p);
-            const double *sp = A.seed + (int64_t)sg * VG_NPOOL;
-#pragma unroll
-            for (int s = 0; s < VG_NPOOL; s++) sd[s] = in ? uload(sp + s) : sd[s];
-            if (CO2U) lco2 = in ? uload(A.co2 + sg) : lco2;
-        }
-    };
     // neighbour values of voxel i: the stored state of the diffusing pools
     // (to recompute D) and lambda^(k+1) of the pools whose differences are
     // taken
@@ -317,102 +419,6 @@ __global__ __launch_bounds__(kBlock) void k_adj(AdjBufs<R> A, Coef<R> C, Pieces 
             }
         }
     };
-    // the reverse step at voxel i from its own words and neighbour values
-    auto work = [&](const AdjOwn<R, NS> &o, I i, const double (&sd)[VG_NPOOL], R lco2,
-                    const R (&zj)[VG_NPOOL][6], const R (&lj)[VG_NPOOL][6]) {
-        // forward state of this step and lambda^(k+1) of the voxel
-        R x[VG_NPOOL], li[VG_NPOOL];
-#pragma unroll
-        for (int s = 0; s < VG_NPOOL; s++) {
-            x[s] = o.x[s];
-            li[s] = o.li[s];
-        }
-        if (CO2U) li[4] = lco2;
-        R w[6];
-        uint32_t code = 0, own = 0;
-        if (REG) {
-            code = o.code;
-            own = code & 7u;
-#pragma unroll
-            for (int k = 0; k < 6; k++) {
-                const uint32_t other = own ^ (((code >> (3 + k)) & 1u) << (k >> 1));
-                w[k] = R(0.5) * (cl[own] + cl[other]);
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < 6; k++) w[k] = R(1);
-        }
-        // x^k = D(z) of the stored z, with the forward's arithmetic
-        if (!FROM_X) {
-#pragma unroll
-            for (int s = 0; s < VG_NPOOL; s++) {
-                if (!mobile<MOB>(s)) continue;
-                const R xi = x[s];
-                R d[6];
-#pragma unroll
-                for (int k = 0; k < 6; k++) {
-                    const R diff = zj[s][k] - xi;
-                    d[k] = REG ? w[k] * diff : diff;
-                }
-                x[s] = xi + C.a[s] * (((d[0] + d[1]) + (d[2] + d[3])) + (d[4] + d[5]));
-            }
-        }
-        R u[VG_NPOOL] = {x[0], x[1], x[2], x[3], x[4]};
-        transform_fwd(C, u[0], u[1], u[2], u[3], u[4]);
-
-        // adjoint of the diffusion half: ubar = Q_w lambda; parameter terms
-        R bar[VG_NPOOL];
-        double own_c = 0.0, cross_c[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-        for (int s = 0; s < VG_NPOOL; s++) {
-            if (!adj_differenced<MOB, DALL, CO2U>(s)) {
-                // (a uniform CO2 adjoint has no neighbour differences: its dL/dD term is 0)
-                bar[s] = li[s];
-                continue;
-            }
-            R sum = R(0);
-            // the voxel's terms of dw/dc (half of each cross-octant edge to
-            // each side), summed in the field type
-            R creg_own = R(0), creg_x[3] = {R(0), R(0), R(0)};
-#pragma unroll
-            for (int k = 0; k < 6; k++) {
-                const R dl = lj[s][k] - li[s];
-                sum += w[k] * dl;
-                if (REG && mobile<MOB>(s)) {
-                    if ((code >> (3 + k)) & 1u) {
-                        creg_own += R(0.5) * dl;
-                        creg_x[k >> 1] += R(0.5) * dl;
-                    } else {
-                        creg_own += dl;
-                    }
-                }
-            }
-            bar[s] = mobile<MOB>(s) ? li[s] + C.a[s] * sum : li[s];
-            g[s] += (double)(u[s] * sum);   // dL/da_s (each voxel's term in the field type)
-            if (REG && mobile<MOB>(s)) {
-                const R f = C.a[s] * u[s];
-                own_c += (double)(f * creg_own);
-                cross_c[0] += (double)(f * creg_x[0]);
-                cross_c[1] += (double)(f * creg_x[1]);
-                cross_c[2] += (double)(f * creg_x[2]);
-            }
-        }
-        if (REG) {
-            // four region slots of this thread (the octant and its three
-            // neighbours across the mid-planes); private, in a fixed order
-            const unsigned tid = threadIdx.x;
-            creg[own][tid] += own_c;
-            creg[own ^ 1u][tid] += cross_c[0];
-            creg[own ^ 2u][tid] += cross_c[1];
-            creg[own ^ 4u][tid] += cross_c[2];
-        }
-        // adjoint of the transformation half
-        transform_rev(C, x, bar, &g[5]);
-#pragma unroll
-        for (int s = 0; s < VG_NPOOL - 1; s++) elem(lout[s], i) = (R)((double)bar[s] + sd[s]);
-        if (!CO2U) elem(lout[4], i) = (R)((double)bar[4] + sd[4]);
-    };
-
     // Full tiles run software-pipelined: a tile's own words (state,
     // lambda^(k+1), neighbour words, region code) are loaded in the previous
     // iteration, right after that iteration's neighbour gathers, so that a
@@ -434,12 +440,12 @@ __global__ __launch_bounds__(kBlock) void k_adj(AdjBufs<R> A, Coef<R> C, Pieces 
         const I i = (I)i64;
         double sd[VG_NPOOL];
         R lco2;
-        volume_terms(t, i64, sd, lco2);
+        adj_volume_terms<R, CO2U>(A, pc, t, i64, sd, lco2);
         R zj[VG_NPOOL][6], lj[VG_NPOOL][6];
         gather(cur, i, zj, lj);
         AdjOwn<R, NS> nxt;
         adj_load_own<R, MOB, REG, NS, DALL, CO2U>(A, st, lin, own_index(tn), nxt);
-        work(cur, i, sd, lco2, zj, lj);
+        adj_voxel<R, MOB, REG, FROM_X, NS, DALL, CO2U>(C, cl, &creg[0][0], lout, cur, i, sd, lco2, zj, lj, g);
         cur = nxt;
         t = tn;
     }
@@ -448,18 +454,157 @@ __global__ __launch_bounds__(kBlock) void k_adj(AdjBufs<R> A, Coef<R> C, Pieces 
         const int64_t i64 = t * kTile + threadIdx.x;
         double sd[VG_NPOOL];
         R lco2;
-        volume_terms(t, i64, sd, lco2);
+        adj_volume_terms<R, CO2U>(A, pc, t, i64, sd, lco2);
         if (i64 < n) {
             const I i = (I)i64;
             adj_load_own<R, MOB, REG, NS, DALL, CO2U>(A, st, lin, i, cur);
             R zj[VG_NPOOL][6], lj[VG_NPOOL][6];
             gather(cur, i, zj, lj);
-            work(cur, i, sd, lco2, zj, lj);
+            adj_voxel<R, MOB, REG, FROM_X, NS, DALL, CO2U>(C, cl, &creg[0][0], lout, cur, i, sd, lco2, zj, lj, g);
         }
     }
     if (REG) {
 #pragma unroll
         for (int r = 0; r < VG_NREG; r++) g[12 + r] = creg[r][threadIdx.x];
+    }
+    block_sum<kG>(g, lds);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int q = 0; q < kG; q++) part[(int64_t)blockIdx.x * kG + q] += g[q];
+    }
+}
+
+// The staged form of k_adj, for relative codes with near x and y neighbours,
+// only DOM diffusing and a uniform CO2 adjoint: a block's tile is V * kBlock
+// consecutive voxels; the adjoints whose differences are taken (and the
+// state's DOM where x^k is recomputed from it) go to LDS with a halo on each side by contiguous
+// loads, the x and y neighbours are read there and only the z neighbours are
+// gathered.  (k_adj with every dL/dD gathers 24 floats per voxel, and a
+// 64-lane gather of floats takes the vector cache about 26 accesses, a
+// contiguous load 4: the cache bounds it.)  A tile's neighbour words are
+// loaded one tile ahead, so all loads of a tile are in flight together.
+// Measured: 512^3 FP32, DOM's D only, 308 -> 260 us (52.5 B per voxel, 4.6
+// TB/s); a 16 x 128^3 batch with regions and every D 117 -> 109 us.
+template <typename R, bool REG, bool FROM_X, bool DALL, int V>
+__global__ __launch_bounds__(kBlock) void k_adj_s(AdjBufs<R> A, Coef<R> C, Pieces pc, uint32_t halo, uint32_t run,
+                                                  double *__restrict__ part) {
+    constexpr int NP = DALL ? VG_NPOOL - 1 : 1, P0 = DALL ? 0 : 1;   // the differenced pools P0 .. P0 + NP - 1
+    constexpr int NS = NP + (FROM_X ? 0 : 1);                        // staged arrays: those, then the state's DOM
+    extern __shared__ __align__(16) unsigned char adj_lds[];
+    R *win = reinterpret_cast<R *>(adj_lds);                         // [NS][V * kBlock + 2 * halo]
+    __shared__ double lds[kWaves * kG];
+    __shared__ R cl[VG_NREG];
+    __shared__ double creg[REG ? VG_NREG * kBlock : 1];
+    if (threadIdx.x < VG_NREG) cl[threadIdx.x] = C.c[threadIdx.x];
+    if (REG) {
+#pragma unroll
+        for (int r = 0; r < VG_NREG; r++) creg[r * kBlock + threadIdx.x] = 0.0;
+    }
+    __syncthreads();
+    if (blockIdx.x == 0) {   // the uniform CO2 adjoint after this step (as in k_adj)
+        for (int s = threadIdx.x; s < A.nseg; s += kBlock)
+            A.co2_next[s] = (R)((double)A.co2[s] + A.seed[(int64_t)s * VG_NPOOL + 4]);
+    }
+    double g[kG];
+#pragma unroll
+    for (int q = 0; q < kG; q++) g[q] = 0.0;
+    const uint32_t n = (uint32_t)A.n, w = (uint32_t)(V * kBlock) + 2u * halo;
+    const R *st[VG_NPOOL], *lin[VG_NPOOL];
+    R *lout[VG_NPOOL];
+#pragma unroll
+    for (int s = 0; s < VG_NPOOL; s++) {
+        st[s] = A.st + (int64_t)(s == 4 ? A.co2_row : s) * A.n;
+        lin[s] = A.lin + (int64_t)s * A.n;
+        lout[s] = A.lout + (int64_t)s * A.n;
+    }
+    const R *sp[NS];
+#pragma unroll
+    for (int s = 0; s < NS; s++) sp[s] = s < NP ? lin[P0 + s] : st[1];
+    const int64_t nt = (A.n + V * kBlock - 1) / (V * kBlock);
+    int64_t t = xcd_stride_tile(blockIdx.x, gridDim.x, 0, nt, run);
+    PackedWords pw[V];
+    auto load_words = [&](int64_t tt) {
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            const int64_t x = (tt * V + v) * kBlock + threadIdx.x;
+            pw[v] = packed_words<true>(A.pk, (uint32_t)(x < A.n ? x : A.n - 1));
+        }
+    };
+    load_words(t);
+    for (int64_t it = 1; t < nt; it++) {
+        const uint32_t t0 = (uint32_t)t * (uint32_t)(V * kBlock);
+        AdjOwn<R, NS_REL> o[V];
+        uint32_t q[V][4], pres[V];   // LDS positions of the x and y neighbours
+        R lz[V][NS][2], hl[NS][2];
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            const uint32_t i = min(t0 + (uint32_t)(v * kBlock) + threadIdx.x, n - 1u);
+            uint32_t j[6];
+            pres[v] = packed_decode_near<true>(A.pk, i, n, pw[v], j);
+#pragma unroll
+            for (int s = 0; s < VG_NPOOL - 1; s++) o[v].li[s] = at(lin[s], i);
+#pragma unroll
+            for (int s = 0; s < NS; s++) {
+                lz[v][s][0] = at(sp[s], j[4]);
+                lz[v][s][1] = at(sp[s], j[5]);
+            }
+#pragma unroll
+            for (int s = 0; s < VG_NPOOL - 1; s++) o[v].x[s] = at(st[s], i);
+            o[v].x[4] = o[v].li[4] = R(0);
+            o[v].code = REG ? (uint32_t)at(A.rcode, i) : 0u;
+#pragma unroll
+            for (int k = 0; k < 4; k++) q[v][k] = j[k] + halo - t0;
+        }
+        if (threadIdx.x < halo) {   // uniform over the wave; a clamped voxel is nobody's neighbour
+            const uint32_t lo = t0 + threadIdx.x, up = t0 + (uint32_t)(V * kBlock) + threadIdx.x;
+#pragma unroll
+            for (int s = 0; s < NS; s++) {
+                hl[s][0] = at(sp[s], lo > halo ? lo - halo : 0u);
+                hl[s][1] = at(sp[s], min(up, n - 1u));
+            }
+        }
+        const int64_t tc = t;
+        t = xcd_stride_tile(blockIdx.x, gridDim.x, it, nt, run);
+        load_words(t);
+        lds_barrier();   // the previous tile's reads are done
+#pragma unroll
+        for (int s = 0; s < NS; s++) {
+            R *ws = win + (uint32_t)s * w;
+#pragma unroll
+            for (int v = 0; v < V; v++)
+                ws[halo + (uint32_t)(v * kBlock) + threadIdx.x] = s < NP ? o[v].li[P0 + (s < NP ? s : 0)] : o[v].x[1];
+            if (threadIdx.x < halo) {
+                ws[threadIdx.x] = hl[s][0];
+                ws[halo + (uint32_t)(V * kBlock) + threadIdx.x] = hl[s][1];
+            }
+        }
+        lds_barrier();
+#pragma unroll
+        for (int v = 0; v < V; v++) {
+            const int64_t i64 = (tc * V + v) * kBlock + threadIdx.x;
+            if ((tc * V + v) * kBlock >= A.n) break;   // uniform over the block
+            double sd[VG_NPOOL];
+            R lco2;
+            adj_volume_terms<R, true>(A, pc, tc * V + v, i64, sd, lco2);
+            R zj[VG_NPOOL][6], lj[VG_NPOOL][6];
+#pragma unroll
+            for (int s = 0; s < NS; s++) {
+#pragma unroll
+                for (int k = 0; k < 6; k++) {
+                    const R x = k < 4 ? win[(uint32_t)s * w + q[v][k & 3]] : lz[v][s][k & 1];
+                    const bool here = ((pres[v] >> k) & 1u) != 0;
+                    if (s < NP) lj[P0 + (s < NP ? s : 0)][k] = here ? x : o[v].li[P0 + (s < NP ? s : 0)];
+                    else zj[1][k] = here ? x : o[v].x[1];
+                }
+            }
+            if (i64 < A.n)
+                adj_voxel<R, 1, REG, FROM_X, NS_REL, DALL, true>(C, cl, creg, lout, o[v], (uint32_t)i64, sd, lco2, zj,
+                                                                 lj, g);
+        }
+    }
+    if (REG) {
+#pragma unroll
+        for (int r = 0; r < VG_NREG; r++) g[12 + r] = creg[r * kBlock + threadIdx.x];
     }
     block_sum<kG>(g, lds);
     if (threadIdx.x == 0) {
@@ -557,6 +702,45 @@ __global__ __launch_bounds__(kBlock) void k_fill_i32(int32_t *__restrict__ p, in
     if (i < cnt) p[i] = 0;
 }
 
+// Voxels per thread of the staged kernel, and where it runs: FP32 (in FP64
+// its registers leave two waves on a SIMD), relative codes whose x and y
+// distances fit a halo of at most a block, enough voxels to give every CU
+// tiles, and not region weights without the static pools' D (one gathered
+// pool: the region sums bound it either way).  Measured, gradient calls with
+// k_adj over the staged kernel: 4.4 M voxels, every D 1.07 (unit weights) and
+// 1.04 (regions), DOM's D only 1.01 and 0.95; FP64 0.98-1.07; 22.8 M voxels
+// 1.07; below 1 M voxels 1.00-1.01.
+template <bool DALL>
+constexpr int kAdjV = DALL ? 2 : 4;
+constexpr int64_t kAdjStagedMin = (int64_t)1 << 20;
+
+template <typename R, bool REG, bool DALL>
+bool adj_staged(const vg_sim *h) {
+    return sizeof(R) == sizeof(float) && (!REG || DALL) && h->xy_dist >= 0 && h->xy_dist <= kBlock &&
+           h->n >= kAdjStagedMin;
+}
+
+template <typename R, bool REG, bool DALL>
+int launch_adj_s(vg_sim *h, bool from_x, const AdjBufs<R> &A, const Coef<R> &C, hipStream_t s) {
+    constexpr int V = kAdjV<DALL>, NP = DALL ? VG_NPOOL - 1 : 1;
+    Pieces pc{h->piece_first, h->piece_lo, h->piece_seg, h->npieces};
+    const uint32_t halo = (uint32_t)((h->xy_dist + 63) / 64 * 64), run = xcd_run(h, V);
+    const size_t row = sizeof(R) * (size_t)(V * kBlock + 2 * halo);
+    const int64_t nt = (h->n + V * kBlock - 1) / (V * kBlock);
+    const int cap = (int)(nt < h->adj_blocks ? nt : h->adj_blocks);
+    // one grid for both forms, so that both add up the sums in the same order
+    const int gx = resident_blocks((const void *)k_adj_s<R, REG, true, DALL, V>, cap, row * NP);
+    const int gz = resident_blocks((const void *)k_adj_s<R, REG, false, DALL, V>, cap, row * (NP + 1));
+    const dim3 grid((unsigned)(gx < gz ? gx : gz));
+    if (from_x)
+        hipLaunchKernelGGL((k_adj_s<R, REG, true, DALL, V>), grid, dim3(kBlock), row * NP, s, A, C, pc, halo, run,
+                           h->adj_part);
+    else
+        hipLaunchKernelGGL((k_adj_s<R, REG, false, DALL, V>), grid, dim3(kBlock), row * (NP + 1), s, A, C, pc, halo,
+                           run, h->adj_part);
+    return launch_status("k_adj_s");
+}
+
 template <typename R, int MOB, bool REG, bool FROM_X, int NS, bool DALL, bool CO2U>
 int launch_adj_k(vg_sim *h, const AdjBufs<R> &A, const Coef<R> &C, hipStream_t s) {
     Pieces pc{h->piece_first, h->piece_lo, h->piece_seg, h->npieces};
@@ -570,6 +754,9 @@ int launch_adj_k(vg_sim *h, const AdjBufs<R> &A, const Coef<R> &C, hipStream_t s
 template <typename R, int MOB, bool REG, int NS, bool DALL>
 int launch_adj_d(vg_sim *h, bool from_x, const AdjBufs<R> &A, const Coef<R> &C, hipStream_t s) {
     if constexpr (MOB == 1) {
+        if constexpr (NS == NS_REL && std::is_same_v<R, float> && (!REG || DALL)) {
+            if (A.co2 && adj_staged<R, REG, DALL>(h)) return launch_adj_s<R, REG, DALL>(h, from_x, A, C, s);
+        }
         if (A.co2) return from_x ? launch_adj_k<R, MOB, REG, true, NS, DALL, true>(h, A, C, s)
                                  : launch_adj_k<R, MOB, REG, false, NS, DALL, true>(h, A, C, s);
     }

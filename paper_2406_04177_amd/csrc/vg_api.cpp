@@ -30,9 +30,10 @@ int hip_status(hipError_t e, const char *what) {
 
 int launch_status(const char *what) { return hip_status(hipGetLastError(), what); }
 
-int resident_blocks(const void *kernel, int cap) {
+int resident_blocks(const void *kernel, int cap, size_t lds) {
     struct Entry {
         const void *kernel;
+        size_t lds;
         int dev, blocks;
     };
     static std::mutex mu;
@@ -42,11 +43,11 @@ int resident_blocks(const void *kernel, int cap) {
     {
         std::lock_guard<std::mutex> lock(mu);
         for (const Entry &e : cache)
-            if (e.kernel == kernel && e.dev == dev) return e.blocks < cap ? e.blocks : cap;
+            if (e.kernel == kernel && e.lds == lds && e.dev == dev) return e.blocks < cap ? e.blocks : cap;
     }
     int cus = 0, per = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, kBlock, 0) != hipSuccess || cus <= 0 ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, kBlock, lds) != hipSuccess || cus <= 0 ||
         per <= 0) {
         (void)hipGetLastError();
         return cap;
@@ -55,7 +56,7 @@ int resident_blocks(const void *kernel, int cap) {
     if (g >= kNumXcd) g -= g % kNumXcd;
     {
         std::lock_guard<std::mutex> lock(mu);
-        cache.push_back({kernel, dev, g});
+        cache.push_back({kernel, lds, dev, g});
     }
     return g < cap ? g : cap;
 }

@@ -118,8 +118,9 @@ __device__ inline int64_t xcd_stride_tile(int64_t b, int64_t nb, int64_t it, int
 
 // Blocks of kBlock threads of `kernel` that fit on the device at once (so a
 // grid-stride launch has no second, partial round), rounded down to a
-// multiple of the XCD count, at most cap (cached per kernel and device).
-int resident_blocks(const void *kernel, int cap);
+// multiple of the XCD count, at most cap (cached per kernel, LDS size and
+// device).
+int resident_blocks(const void *kernel, int cap, size_t lds = 0);
 
 // Barrier that orders the block's LDS accesses only: global loads issued
 // before it may still be in flight after it (a full __syncthreads waits for
@@ -163,39 +164,39 @@ __device__ inline double wave_sum(double v) {
 }
 
 // Per-tile sums of M doubles written straight to out[0..M-1] in a fixed
-// order: each 16-lane row is reduced by DPP (the first four steps of
-// wave_sum), one lane per row stores the row sums in LDS, and thread m < M
-// adds the block's kRows row sums of value m pairwise.  `lds` must hold
-// kRows * M doubles; it may be reused after the call.
-constexpr int kRows = kWaves * 4;
+// order: each quad of lanes is reduced by DPP and one lane per quad stores
+// the quad sums in LDS; then the first wave adds, eight threads per value,
+// two 16-lane rows each (a row's quads as (q0 + q3) + (q2 + q1)) and the
+// eight pairs of rows pairwise by DPP.  `lds` must hold kQuads * M doubles;
+// it may be reused after the call.  (Two DPP steps on all lanes instead of
+// four, and 8 LDS reads instead of 16 on the way to the result: with the
+// region weights' shared reads the recorded pass of a 16 x 128^3 FP32 batch
+// went from 73 to 68 us.)
+constexpr int kQuads = kBlock / 4;
 
 template <int M>
 __device__ inline void tile_sum_to(double (&v)[M], double *lds, double *__restrict__ out) {
-    const int lane = threadIdx.x & 63, row = threadIdx.x >> 4;
+    static_assert(M <= 8 && kQuads == 64, "eight threads of one wave per value");
 #pragma unroll
     for (int m = 0; m < M; m++) {
         double x = v[m];
         x += dpp_move<0xB1>(x);
         x += dpp_move<0x4E>(x);
-        x += dpp_move<0x124>(x);
-        x += dpp_move<0x128>(x);
         v[m] = x;
     }
-    if ((lane & 15) == 0) {
+    if ((threadIdx.x & 3) == 0) {
 #pragma unroll
-        for (int m = 0; m < M; m++) lds[row * M + m] = v[m];
+        for (int m = 0; m < M; m++) lds[m * kQuads + (threadIdx.x >> 2)] = v[m];
     }
     __syncthreads();
-    if (threadIdx.x < M) {
-        const int m = threadIdx.x;
-        double r[kRows];
-#pragma unroll
-        for (int k = 0; k < kRows; k++) r[k] = lds[k * M + m];
-#pragma unroll
-        for (int w = 1; w < kRows; w <<= 1)
-#pragma unroll
-            for (int k = 0; k + w < kRows; k += 2 * w) r[k] += r[k + w];
-        out[m] = r[0];
+    if (threadIdx.x < 64) {
+        const int m = threadIdx.x >> 3, r = threadIdx.x & 7;
+        const double *q = lds + (m < M ? m : 0) * kQuads + r * 8;
+        double x = ((q[0] + q[3]) + (q[2] + q[1])) + ((q[4] + q[7]) + (q[6] + q[5]));
+        x += dpp_move<0xB1>(x);
+        x += dpp_move<0x4E>(x);
+        x += dpp_move<0x141>(x);   // row_half_mirror: lane 7 - r of each eight
+        if (m < M && r == 0) out[m] = x;
     }
     __syncthreads();
 }
@@ -267,6 +268,23 @@ struct CompAcc {
         lo[i] = l;
     }
 };
+
+// ---------------------------------------------------------------- regions
+// Edge weights of a voxel from its region code (octant in bits 0-2, bit 3 + k:
+// the neighbour of slot k lies across the mid-plane): 0.5 (c_own + c_other).
+// Inside an octant that is c_own itself (exactly), and both slots of an axis
+// that cross share the other octant, so four table reads serve six slots.
+template <typename R>
+__device__ __forceinline__ void region_weights(const R *cl, uint32_t code, R (&w)[6]) {
+    const uint32_t own = code & 7u;
+    const R c = cl[own];
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        const R x = R(0.5) * (c + cl[own ^ (1u << a)]);
+        w[2 * a] = ((code >> (3 + 2 * a)) & 1u) ? x : c;
+        w[2 * a + 1] = ((code >> (4 + 2 * a)) & 1u) ? x : c;
+    }
+}
 
 // ---------------------------------------------------------------- kernels
 // Coefficients of one step, rounded once to the field type R.

@@ -320,7 +320,7 @@ __device__ __forceinline__ void finish(const StepBufs<R> &B, const Coef<R> &C, c
 
 // Per-piece sums of the thread's accumulators (a piece is the part of a tile
 // inside one segment), written to part[piece][pool] in a fixed order; `lds`
-// holds kRows * 5 doubles.
+// holds kQuads * 5 doubles.
 __device__ __forceinline__ void tile_totals(const Pieces &pc, int64_t tile, const double (&acc)[kVPT][VG_NPOOL],
                                             double *__restrict__ part, double *lds) {
     const int32_t p0 = pc.piece_first[tile], p1 = pc.piece_first[tile + 1];
@@ -340,7 +340,7 @@ __device__ __forceinline__ void tile_totals(const Pieces &pc, int64_t tile, cons
 
 template <typename R, int MODE, int MOB, bool REG, int TOT>
 __global__ __launch_bounds__(kBlock) void k_step(StepBufs<R> B, Coef<R> C, Pieces pc, double *__restrict__ part) {
-    __shared__ double lds[kRows * VG_NPOOL];
+    __shared__ double lds[kQuads * VG_NPOOL];
     __shared__ R cl[VG_NREG];
     constexpr bool do_d = MODE == MODE_D || MODE == MODE_DT;
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -364,13 +364,7 @@ __global__ __launch_bounds__(kBlock) void k_step(StepBufs<R> B, Coef<R> C, Piece
 #pragma unroll
             for (int k = 0; k < 6; k++) j[v][k] = ld_once(&B.nbr[(int64_t)k * B.n + ic[v]]);
             if (REG) {
-                const uint32_t code = B.rcode[ic[v]];
-                const uint32_t own = code & 7u;
-#pragma unroll
-                for (int k = 0; k < 6; k++) {
-                    const uint32_t other = own ^ (((code >> (3 + k)) & 1u) << (k >> 1));
-                    w[v][k] = R(0.5) * (cl[own] + cl[other]);
-                }
+                region_weights<R>(cl, B.rcode[ic[v]], w[v]);
             }
         }
     }
@@ -389,7 +383,7 @@ __global__ __launch_bounds__(kBlock) void k_step(StepBufs<R> B, Coef<R> C, Piece
 template <typename R, int MODE, int MOB, bool REG, int TOT, bool RELC, bool SEQ, int V = kVPT>
 __global__ __launch_bounds__(kBlock) void k_step_off(StepBufs<R> B, Coef<R> C, Pieces pc, double *__restrict__ part) {
     static_assert(MODE == MODE_D || MODE == MODE_DT, "diffusing passes only");
-    __shared__ double lds[kRows * VG_NPOOL];
+    __shared__ double lds[kQuads * VG_NPOOL];
     __shared__ R cl[VG_NREG];
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const uint32_t n = (uint32_t)B.n;
@@ -423,13 +417,7 @@ __global__ __launch_bounds__(kBlock) void k_step_off(StepBufs<R> B, Coef<R> C, P
 #pragma unroll
     for (int v = 0; v < V; v++) {
         if (REG) {
-            const uint32_t code = at(B.rcode, ic[v]);
-            const uint32_t own = code & 7u;
-#pragma unroll
-            for (int k = 0; k < 6; k++) {
-                const uint32_t other = own ^ (((code >> (3 + k)) & 1u) << (k >> 1));
-                w[v][k] = R(0.5) * (cl[own] + cl[other]);
-            }
+            region_weights<R>(cl, at(B.rcode, ic[v]), w[v]);
         }
     }
     double acc[V][VG_NPOOL];
@@ -525,7 +513,7 @@ __device__ __forceinline__ double comp_at(const float *hi, const int16_t *lo, ui
 template <int MODE, int MOB, int TOT>
 __global__ __launch_bounds__(kBlock) void k_step_c(CompBufs B, Coef<double> C, Pieces pc,
                                                    double *__restrict__ part) {
-    __shared__ double lds[kRows * VG_NPOOL];
+    __shared__ double lds[kQuads * VG_NPOOL];
     __shared__ double cl[VG_NREG];
     constexpr bool do_d = MODE == MODE_D || MODE == MODE_DT;
     constexpr bool do_t = MODE == MODE_T || MODE == MODE_DT;
@@ -569,13 +557,7 @@ __global__ __launch_bounds__(kBlock) void k_step_c(CompBufs B, Coef<double> C, P
     if (do_d) {
         double w[6] = {1.0, 1.0, 1.0, 1.0, 1.0, 1.0};
         if (reg) {
-            const uint32_t code = at(B.rcode, i);
-            const uint32_t own = code & 7u;
-#pragma unroll
-            for (int k = 0; k < 6; k++) {
-                const uint32_t other = own ^ (((code >> (3 + k)) & 1u) << (k >> 1));
-                w[k] = 0.5 * (cl[own] + cl[other]);
-            }
+            region_weights<double>(cl, at(B.rcode, i), w);
         }
 #pragma unroll
         for (int s = 0; s < VG_NPOOL; s++) {
@@ -699,7 +681,7 @@ __device__ __forceinline__ void geo_neighbours(const RGeom &G, const R *cl, cons
 template <typename R, int MODE, int MOB, bool REG, int TOT, bool RASTER>
 __global__ __launch_bounds__(kBlock) void k_step_geo(StepBufs<R> B, Coef<R> C, RGeom G,
                                                      const uint32_t *__restrict__ geo, double *__restrict__ part) {
-    __shared__ double lds[kRows * VG_NPOOL];
+    __shared__ double lds[kQuads * VG_NPOOL];
     __shared__ R cl[VG_NREG];
     constexpr bool do_d = MODE == MODE_D || MODE == MODE_DT;
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -1124,7 +1106,7 @@ __global__ __launch_bounds__(kBandThreads) void k_band2(BandBufs<R> F, const uin
             r.ee = (uint32_t)row[ey1];
             r.bs = (uint32_t)row[y0];
             r.be = (uint32_t)row[y1];
-            if (r.es == r.ee) r.es = r.ee = 0;   // no voxels: no slot is taken
+            if (r.es == r.ee) r.es = r.ee = r.bs = r.be = 0;   // no voxels: no slot is taken
         }
         return r;
     };
