@@ -43,11 +43,12 @@ BYTES_OFFSET_F32 = 5 * 4 + 5 * 4 + 8
 # relative-code kernel: the pools, one 4-byte code word per voxel and 32 B of
 # base distances per 64 voxels
 BYTES_RELATIVE_F32 = 5 * 4 + 5 * 4 + 4 + 32.0 / 64
-# band kernel (two fused passes per launch): per voxel and pass pair the
-# first pass reads four pools and the code word of the band and its two
-# neighbour rows (band of 8 rows: 10/8 of the voxels), the second pass reads
-# four pools and the code word again and writes the five pools; per step half
-BYTES_BAND_F32 = (10.0 / 8 * (4 * 4 + 4 + 32.0 / 64) + (4 * 4 + 4 + 32.0 / 64) + 5 * 4) / 2
+# band kernel (two fused passes per launch): per voxel and pass pair DOM of the
+# band and two neighbour rows on each side, the other four pools and the code
+# word of the band and one neighbour row on each side (bands of 12 rows at
+# 512^3 in FP32 and FP64), and the five pools written; per step half
+BYTES_BAND_F32 = (16.0 / 12 * 4 + 14.0 / 12 * (4 * 4 + 4 + 32.0 / 64) + 5 * 4) / 2
+BYTES_BAND_F64 = (16.0 / 12 * 8 + 14.0 / 12 * (4 * 8 + 4 + 32.0 / 64) + 5 * 8) / 2
 # compensated FP32 fields: the method's algorithmic count with 6-byte values
 BYTES_FUSED_F32C = 5 * 6 + 5 * 6 + 6 * 4
 # compensated FP32 fields (float + 16-bit word per value), relative codes:
@@ -839,8 +840,8 @@ def main(argv=None):
     ms_step = ms / K
     vps = n * K / (ms / 1e3)
     # the dominant kernel's own average launch time: K2 = 4 m + 1 paper steps
-    # launch a transformation-only pass, 4 m fused passes (m runs of four: 2 m
-    # band launches, or 4 m single passes) and a diffusion-only pass, one step
+    # launch a transformation-only pass, 4 m fused passes (2 m band launches of
+    # two, or 4 m single passes) and a diffusion-only pass, one step
     # launches the two end passes only; no totals in either
     ppl = PASSES_PER_LAUNCH[kernel]
     K2 = (K - 1) // 4 * 4 + 1
@@ -857,7 +858,7 @@ def main(argv=None):
     elif prec == "f32c":
         own_bpv, bpv = BYTES_COMP_RELATIVE if kernel == 4 else BYTES_FUSED_F32C, BYTES_FUSED_F32C
     else:
-        own_bpv, bpv = BYTES_F64_RELATIVE if kernel == 4 else BYTES_FUSED_F64, BYTES_FUSED_F64
+        own_bpv, bpv = {4: BYTES_F64_RELATIVE, 5: BYTES_BAND_F64}.get(kernel, BYTES_FUSED_F64), BYTES_FUSED_F64
     achieved = bpv * ppl * n / (us_launch / 1e6) / 1e9
     kname = KERNEL_FUNCS[kernel] if prec != "f32c" else "k_step_c (compensated FP32, relative codes)"
     traffic = None

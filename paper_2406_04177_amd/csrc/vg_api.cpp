@@ -357,6 +357,77 @@ bool graphs_wanted(const vg_sim *h) {
     return h->n <= ((int64_t)1 << 19);   // measured: 1.35x at 48^3, 1.02x at 128^3, none from 256^3
 }
 
+// Passes over slabs, for compensated fields.  Where they outgrow the 256 MB
+// last-level cache, consecutive passes run slab by slab: all passes of a
+// group on one slab of tiles (kSlabBytes of fields) before the next slab, so
+// that every pass but the first finds its slab in that cache.  Pass k + 1
+// stays behind pass k by the largest neighbour distance, so its inputs are
+// complete and nothing it overwrites is still to be read; the passes, their
+// order per voxel and the totals' partials are those of whole passes
+// (bit-identical).  Tiles go to the XCDs in runs of an eighth of a plane,
+// whose z neighbours are then in the XCD's own L2.
+// Measured at 512^3 (64.5 B per voxel and pass, 10 steps): whole passes 3.44
+// ms; slabs of 64, 96, 128, 192 MB 3.32, 3.01, 2.90 and 2.95 ms, with runs of
+// an eighth of a plane 2.84-2.97.  A launch's start and end cost about 5 us, so
+// smaller slabs lose (32 MB 4.15 ms), as do fields that fit the cache.
+// (Plain fields on single passes, as with region weights, gained 1.04-1.16,
+// but the range cost a 48^3 pass 3 %, and a second instance of every pass is
+// not worth it.)
+constexpr double kSlabBytes = 192e6, kSlabMinBytes = 256e6;
+constexpr int kSlabPasses = 16;      // passes of a group
+
+struct PassDesc {
+    int mode, tot;
+    double dt_t, dt_d;
+};
+
+double pass_bytes_per_voxel(const vg_sim *h) {
+    return (h->mobile_all ? 10.0 : 6.0) * 6.0 + 4.5;
+}
+
+int64_t slab_skew(const vg_sim *h) {   // tiles
+    return (std::max(h->xy_dist, h->z_dist) + kTile - 1) / kTile;
+}
+
+bool use_slabs(const vg_sim *h) {
+    if (h->prec != VG_F32C || h->z_dist < 0 || !(use_relative(h) || use_offsets(h))) return false;
+    const double bytes = pass_bytes_per_voxel(h);
+    if ((double)h->n * bytes < kSlabMinBytes) return false;
+    return (double)slab_skew(h) * kTile * kSlabPasses * bytes < 0.5 * kSlabBytes;
+}
+
+// The passes of a group (their totals in consecutive slots from the current one).
+int run_slabs(vg_sim *h, const std::vector<PassDesc> &group, hipStream_t s) {
+    const int T = (int)group.size(), cur0 = h->cur, slot0 = h->part_slot;
+    const int64_t skew = slab_skew(h), nt = h->ntiles;
+    const int64_t slab = std::max<int64_t>(1, (int64_t)(kSlabBytes / pass_bytes_per_voxel(h) / kTile));
+    std::vector<int64_t> done((size_t)T, 0);
+    int logged = 0, rc = VG_OK;
+    for (int64_t q = 1; done[T - 1] < nt; q++) {
+        const bool last = q * slab >= nt;
+        h->cur = cur0;
+        logged = 0;
+        for (int k = 0; k < T; k++) {
+            const PassDesc &p = group[k];
+            const int64_t to = last ? nt : std::max<int64_t>(0, q * slab - k * skew);
+            h->part_slot = slot0 + logged;
+            const int cur = h->cur;
+            if (to > done[k]) {
+                TileRange tr;
+                tr.t0 = done[k];
+                tr.t1 = to;
+                tr.run = xcd_run(h, 1);
+                if ((rc = launch_pass2(h, p.mode, p.tot, p.dt_t, p.dt_d, s, &tr))) return rc;
+                done[k] = to;
+            }
+            h->cur = (p.mode == MODE_D || p.mode == MODE_DT) ? cur ^ 1 : cur;
+            if (p.tot != TOT_NONE) logged++;
+        }
+    }
+    h->part_slot = slot0 + logged;
+    return rc;
+}
+
 constexpr int64_t kRunPasses = 16;   // fused passes per captured run (a multiple of 4: band runs)
 
 // Launches (capturing it first if needed) a run of kRunPasses fused passes
@@ -574,6 +645,28 @@ extern "C" int vg_step_explicit(vg_sim *h, int64_t nsteps, double dt, int64_t lo
         if (++h->part_slot < h->tot_batch) return VG_OK;
         return flush();
     };
+    if (use_slabs(h)) {
+        std::vector<PassDesc> group;
+        const bool td = h->params.step_order == VG_ORDER_TD;
+        const int64_t npass = td ? nsteps + 1 : nsteps;
+        for (int64_t q = 0; q < npass; q++) {
+            // the paper's order: T, fused passes with the state of step q between their halves, D
+            PassDesc p{MODE_DT, TOT_NONE, dt, dt};
+            if (td && q == 0) p.mode = MODE_T;
+            else if (td && q == nsteps) p = {MODE_D, logged(q) ? TOT_OUT : TOT_NONE, dt, dt};
+            else if (td) p.tot = logged(q) ? TOT_MID : TOT_NONE;
+            else p.tot = logged(q + 1) ? TOT_OUT : TOT_NONE;
+            group.push_back(p);
+            int slots = 0;
+            for (const PassDesc &g : group) slots += g.tot != TOT_NONE;
+            if ((int)group.size() == kSlabPasses || slots == h->tot_batch || q + 1 == npass) {
+                if ((rc = run_slabs(h, group, s))) return rc;
+                group.clear();
+                if ((rc = flush())) return rc;
+            }
+        }
+        return restore_canonical(h, s);
+    }
     // fused passes with no totals logged run in pairs on the band kernel
     // where it applies; each launch moves the state to the other field set,
     // and a single fused pass can take it back

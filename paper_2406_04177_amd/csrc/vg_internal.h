@@ -93,6 +93,14 @@ __device__ inline int64_t xcd_tile(int64_t b, int64_t nb) {
     return ((k / S) * kNumXcd + x) * S + k % S;
 }
 
+// The same with runs of S tiles.
+__device__ inline int64_t xcd_tile_run(uint32_t b, uint32_t nb, uint32_t S) {
+    const uint32_t R = S * (uint32_t)kNumXcd, full = nb / R * R;
+    if (b >= full) return full + xcd_split(b - full, nb - full);
+    const uint32_t x = b % kNumXcd, k = b / kNumXcd;
+    return ((k / S) * kNumXcd + x) * S + k % S;
+}
+
 // Tile of iteration `it` of block b in a grid-stride kernel of nb blocks.
 // With nb a multiple of 8 the blocks of one XCD (b % 8) walk that XCD's own
 // runs of S consecutive tiles (runs dealt to the XCDs in turn, as in
@@ -647,7 +655,13 @@ inline uint32_t xcd_run(const vg_sim *h, int V) {
 enum { MODE_T = 0, MODE_D = 1, MODE_DT = 2, MODE_NONE = 3 };
 enum { TOT_NONE = 0, TOT_IN = 1, TOT_MID = 2, TOT_OUT = 3 };
 int launch_pass(vg_sim *h, int mode, int tot, double dt, hipStream_t s);
-int launch_pass2(vg_sim *h, int mode, int tot, double dt_t, double dt_d, hipStream_t s);
+// Reduction tiles [t0, t1) of a pass that covers part of the voxels
+// (compensated fields), dealt to the XCDs in runs of `run` tiles.
+struct TileRange {
+    int64_t t0 = 0, t1 = 0;
+    uint32_t run = 0;
+};
+int launch_pass2(vg_sim *h, int mode, int tot, double dt_t, double dt_d, hipStream_t s, const TileRange *tr = nullptr);
 int launch_pass_bufs(vg_sim *h, int mode, int tot, double dt, const void *const src[VG_NPOOL],
                      void *const dst[VG_NPOOL], hipStream_t s, void *xdom = nullptr);
 // Reduces the partials of slots 0 .. rows-1 into rows consecutive totals

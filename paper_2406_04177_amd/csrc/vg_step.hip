@@ -504,20 +504,23 @@ struct CompBufs {
     float *dst[VG_NPOOL] = {};
     int16_t *dlo[VG_NPOOL] = {};
     int64_t n = 0;
+    TileRange tr;                       // the tiles the pass covers (t1 = 0: all)
 };
 
 __device__ __forceinline__ double comp_at(const float *hi, const int16_t *lo, uint32_t i) {
     return comp_get(at(hi, i), at(lo, i));
 }
 
-template <int MODE, int MOB, int TOT>
+// SLAB: the pass covers the tiles B.tr (see the slabs of vg_api.cpp).
+template <int MODE, int MOB, int TOT, bool SLAB>
 __global__ __launch_bounds__(kBlock) void k_step_c(CompBufs B, Coef<double> C, Pieces pc,
                                                    double *__restrict__ part) {
     __shared__ double lds[kQuads * VG_NPOOL];
     __shared__ double cl[VG_NREG];
     constexpr bool do_d = MODE == MODE_D || MODE == MODE_DT;
     constexpr bool do_t = MODE == MODE_T || MODE == MODE_DT;
-    const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int64_t tile = SLAB ? B.tr.t0 + xcd_tile_run(blockIdx.x, gridDim.x, B.tr.run)
+                              : xcd_tile(blockIdx.x, gridDim.x);
     const uint32_t n = (uint32_t)B.n;
     const bool reg = B.rcode != nullptr;
     if (reg) {   // uniform over the block
@@ -1274,7 +1277,12 @@ __global__ __launch_bounds__(kBandThreads) void k_band2(BandBufs<R> F, const uin
 template <int MODE, int MOB, int TOT>
 int launch_c(vg_sim *h, const CompBufs &B, const Coef<double> &C, hipStream_t s) {
     Pieces pc{h->piece_first, h->piece_lo, h->piece_seg, h->npieces};
-    hipLaunchKernelGGL((k_step_c<MODE, MOB, TOT>), dim3((unsigned)h->ntiles), dim3(kBlock), 0, s, B, C, pc, part_of(h));
+    if (B.tr.t1 > 0)
+        hipLaunchKernelGGL((k_step_c<MODE, MOB, TOT, true>), dim3((unsigned)(B.tr.t1 - B.tr.t0)), dim3(kBlock), 0, s, B,
+                           C, pc, part_of(h));
+    else
+        hipLaunchKernelGGL((k_step_c<MODE, MOB, TOT, false>), dim3((unsigned)h->ntiles), dim3(kBlock), 0, s, B, C, pc,
+                           part_of(h));
     return launch_status("k_step_c");
 }
 
@@ -1290,8 +1298,9 @@ int pick_tot_c(vg_sim *h, int tot, const CompBufs &B, const Coef<double> &C, hip
 
 // A pass on compensated fields: the same buffer rotation as dispatch<R>, for
 // the float parts and the compensation words alike.
-int dispatch_c(vg_sim *h, int mode, int tot, double dt_t, double dt_d, hipStream_t s) {
+int dispatch_c(vg_sim *h, int mode, int tot, double dt_t, double dt_d, const TileRange *tr, hipStream_t s) {
     CompBufs B;
+    if (tr) B.tr = *tr;
     B.nbr = h->nbr;
     B.rcode = h->rcode;
     B.pk = packed_of(h);
@@ -1597,9 +1606,9 @@ int launch_geometry(vg_sim *h, hipStream_t s) {
     return launch_status("k_geometry");
 }
 
-int launch_pass2(vg_sim *h, int mode, int tot, double dt_t, double dt_d, hipStream_t s) {
+int launch_pass2(vg_sim *h, int mode, int tot, double dt_t, double dt_d, hipStream_t s, const TileRange *tr) {
     if (h->n == 0) return VG_OK;
-    if (h->prec == VG_F32C) return dispatch_c(h, mode, tot, dt_t, dt_d, s);
+    if (h->prec == VG_F32C) return dispatch_c(h, mode, tot, dt_t, dt_d, tr, s);
     if (h->prec == VG_F64) return dispatch<double>(h, mode, tot, dt_t, dt_d, s);
     return dispatch<float>(h, mode, tot, dt_t, dt_d, s);
 }
