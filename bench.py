@@ -70,12 +70,9 @@ KERNEL_SOURCES = ("paper_2406_04177_amd/csrc/vg_step.hip", "paper_2406_04177_amd
                   "paper_2406_04177_amd/build.py")
 MEASURED_TRAFFIC = {
     # (kernel, size): (bytes per launch, sha256 of KERNEL_SOURCES); from
-    # profiles/k_band2_f32_512cube.md: FETCH_SIZE 593521.3 KiB x 2 +
-    # WRITE_SIZE 412398.7 KiB x 1 per launch (two fused passes), and
-    # profiles/k_step_c_f32c_512cube.md: FETCH_SIZE 479815.7 KiB x 2 +
-    # WRITE_SIZE 614750.5 KiB per launch (one pass, compensated FP32)
-    ("band", 512): (593521.3 * 1024 * 2 + 412398.7 * 1024, "69b7e38df9ad0daa574489029c012a67ae0251ed2b47373b68c9c967b88515e5"),
-    ("relative_f32c", 512): (479815.7 * 1024 * 2 + 614750.5 * 1024, "69b7e38df9ad0daa574489029c012a67ae0251ed2b47373b68c9c967b88515e5"),
+    # profiles/k_band2_f32_512cube.md: FETCH_SIZE 275053.6 KiB x 2 +
+    # WRITE_SIZE 409254.5 KiB x 1 per launch (two fused passes)
+    ("band", 512): (275053.6 * 1024 * 2 + 409254.5 * 1024, "429cd7dc3c26e205d9919fd2e7b11ef7135c60a8f7797c301deba43fbd46ea29"),
 }
 
 
