@@ -97,8 +97,8 @@ size_t layout(vg_sim *h, char *base) {
         h->cg_m = (double *)take(nd);
         h->cg_p[0] = (double *)take(nd);
         h->cg_p[1] = (double *)take(nd);
-        h->cg_part = (double *)take(sizeof(double) * 4 * (size_t)h->cg_blocks);
-        h->cg_scal = (double *)take(sizeof(double) * 16);
+        h->cg_part = (double *)take(sizeof(double) * kCgParts * (size_t)h->cg_blocks);
+        h->cg_scal = (double *)take(sizeof(double) * kCgScal);
     }
     if (h->features & VG_FEAT_MG) {
         // the hierarchy at the capacities mg_plan reserved (set-up scratch:

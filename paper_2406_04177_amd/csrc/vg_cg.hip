@@ -9,16 +9,24 @@
 // to move as few bytes as it can:
 //  - k_cg_dot: the partials of (z, B z), a gather of z and the neighbour
 //    words and nothing else (12.5 B per voxel).  (p, B p) follows from it:
-//    with p = z + beta p_old, z.r_old = 0 and p.B p_old = 0,
-//    (p, B p) = (z, B z) - beta (r.z) / alpha_old
-//    (Chronopoulos and Gear, J. Comput. Appl. Math. 25, 1989);
+//    with p = z + beta p_old and q_old = B p_old,
+//    (p, B p) = (z, B z) + 2 beta (z, q_old) + beta^2 (p_old, q_old),
+//    whose last two products the step before sums where z and q_old are in
+//    registers.  (The orthogonality of z and r_old would give them for free
+//    as -beta (r.z) / alpha_old together - Chronopoulos and Gear, J. Comput.
+//    Appl. Math. 25, 1989 - but rounding loses it on ill-conditioned systems:
+//    a 12^3 cube at a = 1e12 never converged and a chain of 400 at a = 1e6
+//    took 1.3 times the iterations.  The summed products keep the iteration
+//    counts of a directly summed (p, B p); beside the recurrence they cost an
+//    iteration 0.6 us (3 %) at 128^3, nothing measurable at 512^3, and the
+//    multigrid's 2 %.)
 //  - k_cg_step: p = z + beta p_old for the voxel and its neighbours, so that
 //    q = B p is formed in registers and never stored; z <- z - alpha M^-1 q
 //    into the other z buffer (r = M z is not stored: r_i is z_i times the
 //    diagonal), p into the other p buffer, and every second iteration
 //    x += alpha_old p_old + alpha p (a last odd direction is added on
-//    write-back); the partials of r.z and r.r.  28.5 B read, 16 B written per
-//    voxel and 16 B for x every second iteration.
+//    write-back); the partials of r.z, r.r, (p, q) and (z, q).  20.5 B read,
+//    16 B written per voxel and 16 B for x every second iteration.
 // 57 B per voxel and iteration on average.  (The form before it stored q, r
 // and updated x each time: 93.5 B; 512^3, 22.8 M voxels: see k_cg_step.)
 // There is no kernel for the scalars: each block of the kernel that needs
@@ -53,7 +61,9 @@
 // lie in its own block (their terms vanish) and the others in the three
 // coarse neighbours on its side, so this kernel gathers only from the four
 // times smaller coarse solution.  With the multigrid r is kept (in place of
-// the z update) and the V-cycle writes z and the r.z partials.
+// the z update: 28.5 B read by k_cg_step), the V-cycle writes z and the r.z
+// partials, and k_cg_dot, which has B z in registers, sums (z, q_old) as
+// (B z, p_old) (20.5 B).
 #include <type_traits>
 
 #include "vg_internal.h"
@@ -63,10 +73,13 @@ namespace {
 
 // Scalars on the device: r.z and alpha of the current and the previous
 // iteration (slot = iteration & 1), r.r, b.b, the convergence flag, the
-// iterations done and the squared tolerance.
-enum { S_RZ = 0, S_ALPHA = 2, S_RR = 4, S_BB, S_DONE, S_ITER, S_RTOL2, S_NSCAL = 9 };
-// Partials per block, one array of CgArgs::ldp each: r.z, r.r, b.b, z.Bz.
-enum { P_RZ = 0, P_RR, P_BB, P_ZBZ };
+// iterations done, the squared tolerance, and (p, q) and (z, q) of the
+// iteration before (z the one after it).
+enum { S_RZ = 0, S_ALPHA = 2, S_RR = 4, S_BB, S_DONE, S_ITER, S_RTOL2, S_PQ, S_ZQ, S_NSCAL };
+// Partials per block, one array of CgArgs::ldp each: r.z, (z, q), (p, q),
+// r.r (k_cg_step's, in this order), b.b, z.Bz.
+enum { P_RZ = 0, P_ZQ, P_PQ, P_RR, P_BB, P_ZBZ, P_N };
+static_assert(S_NSCAL <= kCgScal && P_N == kCgParts, "the workspace layout's sizes");
 
 // The gathering kernels come in two forms.  A 64-lane load of doubles takes
 // the vector cache 16 cycles whatever its addresses (measured: 17.8 accesses
@@ -236,36 +249,49 @@ __device__ __forceinline__ void cg_stage(double *win, const double (&own)[kCgTil
     lds_barrier();
 }
 
-// Sum of the G per-block partials of a slot, the same in every thread of the
-// block, in a fixed order.  lds: kWaves doubles.
-__device__ __forceinline__ double reduce_parts(const double *__restrict__ part, int G,
-                                               double *lds) {
+// Sums of the G[m] per-block partials of M slots, the same in every thread of
+// the block, in a fixed order.  lds: kWaves * M doubles.
+template <int M>
+__device__ __forceinline__ void reduce_parts(const double *const (&part)[M], const int (&G)[M], double *lds,
+                                             double (&out)[M]) {
     // all loads in flight at once (one after the other they cost the start of
     // the kernel a memory latency each)
     constexpr int U = kCgMaxBlocks / kBlock;
-    double x[U];
+    double x[M][U];
 #pragma unroll
-    for (int u = 0; u < U; u++) {
-        const int b = u * kBlock + (int)threadIdx.x;
-        x[u] = b < G ? part[b] : 0.0;
+    for (int m = 0; m < M; m++)
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int b = u * kBlock + (int)threadIdx.x;
+            x[m][u] = b < G[m] ? part[m][b] : 0.0;
+        }
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+        double v = x[m][0];
+#pragma unroll
+        for (int u = 1; u < U; u++) v += x[m][u];
+        v = wave_sum(v);
+        if ((threadIdx.x & 63) == 0) lds[m * kWaves + (threadIdx.x >> 6)] = v;
     }
-    double v = x[0];
+    __syncthreads();
 #pragma unroll
-    for (int u = 1; u < U; u++) v += x[u];
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    for (int m = 0; m < M; m++) {
+        out[m] = lds[m * kWaves];
+        for (int w = 1; w < kWaves; w++) out[m] += lds[m * kWaves + w];
+    }
     __syncthreads();
-    v = lds[0];
-    for (int w = 1; w < kWaves; w++) v += lds[w];
-    __syncthreads();
-    return v;
+}
+__device__ __forceinline__ double reduce_parts(const double *__restrict__ part, int G, double *lds) {
+    const double *const p[1] = {part};
+    const int g[1] = {G};
+    double v[1];
+    reduce_parts<1>(p, g, lds, v);
+    return v[0];
 }
 
-// Convergence of iterate k (k iterations done) from the G partials of r.r;
-// block 0 keeps the scalars.  True in every thread once converged.
-__device__ __forceinline__ bool cg_check(const double *__restrict__ rr_part, int G, int k, double bb,
-                                         double *__restrict__ scal, double *lds) {
-    const double rr = reduce_parts(rr_part, G, lds);
+// Convergence of iterate k (k iterations done) from its r.r; block 0 keeps the
+// scalars.  True in every thread once converged.
+__device__ __forceinline__ bool cg_check(double rr, int k, double bb, double *__restrict__ scal) {
     const bool done = rr <= scal[S_RTOL2] * bb;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         scal[S_RR] = rr;
@@ -317,33 +343,49 @@ __global__ __launch_bounds__(kBlock) void k_cg_init(CgArgs A, F field, double *_
     }
     block_sum<3>(acc, lds);
     if (threadIdx.x == 0) {
-        for (int u = MG ? 1 : 0; u < 3; u++) part[u * A.ldp + (int)blockIdx.x] = acc[u];
+        if (!MG) part[P_RZ * A.ldp + (int)blockIdx.x] = acc[0];
+        part[P_RR * A.ldp + (int)blockIdx.x] = acc[1];
+        part[P_BB * A.ldp + (int)blockIdx.x] = acc[2];
     }
 }
 
-// Partials of (z, B z) of iteration k; before that r.z of iterate k from its
-// Gp partials, and for Jacobi the convergence check (the V-cycle has done it).
+// Partials of (z, B z) of iteration k (MG: and of (B z, p_old)); before that
+// r.z of iterate k from its Gp partials, (p, q) and (z, q) of the iteration
+// before from its Gs, and for Jacobi the convergence check (the V-cycle has
+// done it).
 // In every gathering kernel a tile's neighbour words are loaded one tile
 // ahead, so that its gathers wait for nothing; the staged window is double
 // buffered (one barrier per tile).
 // 512^3 (22.8 M voxels): 125 us direct, 92 us staged (12.5 B per voxel).
 template <bool REG, int NS, bool MG, int V>
-__global__ __launch_bounds__(kBlock) void k_cg_dot(CgArgs A, int k, int Gp, const double *__restrict__ z,
-                                                   double *__restrict__ scal, double *__restrict__ part) {
+__global__ __launch_bounds__(kBlock) void k_cg_dot(CgArgs A, int k, int Gp, int Gs, const double *__restrict__ z,
+                                                   const double *__restrict__ pold, double *__restrict__ scal,
+                                                   double *__restrict__ part) {
     if (scal[S_DONE] != 0.0) return;
     constexpr bool ST = V > 1;
     __shared__ double win[ST ? 2 : 1][ST ? kCgWin : 1];
-    __shared__ double lds[kWaves * 2];
+    __shared__ double lds[kWaves * 3];
     __shared__ double cl[VG_NREG];
     if (threadIdx.x < VG_NREG) cl[threadIdx.x] = A.c[threadIdx.x];
     __syncthreads();
-    if (!MG && cg_check(part + P_RR * A.ldp, Gp, k, scal[S_BB], scal, lds)) return;
+    // block 0 adds up what the next kernel needs, in one go (one sum after the
+    // other would hold up the kernel; before the first direction (z, q) and
+    // (p, q) hold nothing and are not used)
     if (blockIdx.x == 0) {
-        const double rz = reduce_parts(part + P_RZ * A.ldp, Gp, lds);
-        if (threadIdx.x == 0) scal[S_RZ + (k & 1)] = rz;
+        const double *const p[3] = {part + P_RZ * A.ldp, part + P_ZQ * A.ldp, part + P_PQ * A.ldp};
+        const int G[3] = {Gp, MG || k == 0 ? 0 : Gs, k == 0 ? 0 : Gs};
+        double v[3];
+        reduce_parts<3>(p, G, lds, v);
+        if (threadIdx.x == 0) {
+            scal[S_RZ + (k & 1)] = v[0];
+            scal[S_ZQ] = v[1];
+            scal[S_PQ] = v[2];
+        }
     }
+    if (!MG && cg_check(reduce_parts(part + P_RR * A.ldp, Gp, lds), k, scal[S_BB], scal)) return;
+    const bool first = k == 0;   // p_old holds nothing before the first direction
     const int64_t nt = (A.n + kBlock * V - 1) / (kBlock * V);
-    double acc[1] = {0.0};
+    double acc[MG ? 2 : 1] = {};
     int64_t t = xcd_stride_tile(blockIdx.x, gridDim.x, 0, nt, A.run);
     CgIdx<NS> i[V];
     bool act[V];
@@ -354,6 +396,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_dot(CgArgs A, int k, int Gp, cons
     for (int64_t it = 1; t < nt; it++) {
         bool pres[V][6];
         double zi[V], zj[V][6];
+        [[maybe_unused]] double po[V];
         [[maybe_unused]] uint32_t q[V][4];
         [[maybe_unused]] double hz[2];
 #pragma unroll
@@ -361,6 +404,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_dot(CgArgs A, int k, int Gp, cons
             CgIdx<NS> j[6];
             cg_decode<NS>(A, i[v], w[v], j, pres[v]);
             zi[v] = el(z, i[v]);
+            if constexpr (MG) po[v] = first ? 0.0 : el(pold, i[v]);
 #pragma unroll
             for (int k6 = ST ? 4 : 0; k6 < 6; k6++) zj[v][k6] = el(z, j[k6]);
             if constexpr (ST) {
@@ -396,20 +440,26 @@ __global__ __launch_bounds__(kBlock) void k_cg_dot(CgArgs A, int k, int Gp, cons
                 const double wt = weight(A.rcode, cl, i[v], k6, REG);
                 s += pres[v][k6] ? wt * (zi[v] - zj[v][k6]) : 0.0;
             }
-            acc[0] += act[v] ? zi[v] * (zi[v] + A.a * s) : 0.0;
+            const double bz = zi[v] + A.a * s;
+            acc[0] += act[v] ? zi[v] * bz : 0.0;
+            if constexpr (MG) acc[1] += act[v] ? po[v] * bz : 0.0;
             i[v] = in[v];
             act[v] = an[v];
         }
     }
-    block_sum<1>(acc, lds);
-    if (threadIdx.x == 0) part[P_ZBZ * A.ldp + (int)blockIdx.x] = acc[0];
+    block_sum<MG ? 2 : 1>(acc, lds);
+    if (threadIdx.x == 0) {
+        part[P_ZBZ * A.ldp + (int)blockIdx.x] = acc[0];
+        if constexpr (MG) part[P_ZQ * A.ldp + (int)blockIdx.x] = acc[1];
+    }
 }
 
-// Iteration k's update: alpha and beta from the Gp partials of (z, B z), p = z + beta p_old
-// (for the neighbours too), q = B p, then z' = z - alpha M^-1 q (Jacobi, into
-// zr) or r -= alpha q (MG, zr in place).  Odd k also add the last two
-// directions to y.  512^3: 325 us direct, 255 us staged (52.5 B per voxel on
-// average); the two kernels that stored q and r took 343 and 151 us.
+// Iteration k's update: alpha and beta from the Gp partials of (z, B z) (MG: and (z, q_old)),
+// p = z + beta p_old (for the neighbours too), q = B p, then z' = z - alpha
+// M^-1 q (Jacobi, into zr) or r -= alpha q (MG, zr in place).  Odd k also add
+// the last two directions to y.  512^3: 325 us direct, 255 us staged (44.5 B
+// per voxel on average); the two kernels that stored q and r took 343 and
+// 151 us.
 template <bool REG, int NS, bool MG, int V>
 __global__ __launch_bounds__(kBlock) void k_cg_step(CgArgs A, int k, int Gp, const double *__restrict__ z,
                                                     const double *__restrict__ pold, double *__restrict__ pnew,
@@ -419,20 +469,37 @@ __global__ __launch_bounds__(kBlock) void k_cg_step(CgArgs A, int k, int Gp, con
     constexpr bool ST = V > 1;
     __shared__ double win[ST ? 2 : 1][ST ? kCgWin : 1];
     __shared__ double lds[kWaves * 2];
+    __shared__ double sum[kQuads * (MG ? 2 : 4)];
     __shared__ double cl[VG_NREG];
     __shared__ double mtab[8];
     if (threadIdx.x < VG_NREG) cl[threadIdx.x] = A.c[threadIdx.x];
     if (!MG && !REG && threadIdx.x < 7) mtab[threadIdx.x] = 1.0 / (1.0 + A.a * (double)threadIdx.x);
     __syncthreads();
-    const double zbz = reduce_parts(part + P_ZBZ * A.ldp, Gp, lds);
+    double zbz, zq;   // (z, B z) and (z, q_old)
+    if constexpr (MG) {
+        const double *const p[2] = {part + P_ZBZ * A.ldp, part + P_ZQ * A.ldp};
+        const int G[2] = {Gp, Gp};
+        double v[2];
+        reduce_parts<2>(p, G, lds, v);
+        zbz = v[0];
+        zq = v[1];
+    } else {
+        zbz = reduce_parts(part + P_ZBZ * A.ldp, Gp, lds);
+        zq = scal[S_ZQ];
+    }
     const double rz = scal[S_RZ + (k & 1)];
     const double aold = k > 0 ? scal[S_ALPHA + ((k & 1) ^ 1)] : 0.0;
-    const double beta = k > 0 ? rz / scal[S_RZ + ((k & 1) ^ 1)] : 0.0;
-    const double alpha = k > 0 ? rz / (zbz - beta * rz / aold) : rz / zbz;
+    double beta = k > 0 ? rz / scal[S_RZ + ((k & 1) ^ 1)] : 0.0;
+    double pbp = k > 0 ? zbz + beta * (2.0 * zq + beta * scal[S_PQ]) : zbz;
+    if (pbp <= 0.0) {   // lost to rounding (B is positive definite): restart from p = z
+        beta = 0.0;
+        pbp = zbz;
+    }
+    const double alpha = rz / pbp;
     if (blockIdx.x == 0 && threadIdx.x == 0) scal[S_ALPHA + (k & 1)] = alpha;
     const bool add = (k & 1) != 0, first = k == 0;   // p_old holds nothing before the first direction
     const int64_t nt = (A.n + kBlock * V - 1) / (kBlock * V);
-    double acc[2] = {0.0, 0.0};
+    double acc[MG ? 2 : 4] = {};   // (r.z, (z, q),) (p, q), r.r
     int64_t t = xcd_stride_tile(blockIdx.x, gridDim.x, 0, nt, A.run);
     CgIdx<NS> i[V];
     bool act[V];
@@ -519,18 +586,20 @@ __global__ __launch_bounds__(kBlock) void k_cg_step(CgArgs A, int k, int Gp, con
                 el(pnew, i[v]) = pi[v];
                 if (add) el(y, i[v]) = yi[v] + (aold * po[v] + alpha * pi[v]);
                 el(zr, i[v]) = MG ? rn : zn;
-                acc[0] += rn * zn;
-                acc[1] += rn * rn;
+                constexpr int Q = MG ? 0 : 2;
+                if constexpr (!MG) {
+                    acc[0] += rn * zn;
+                    acc[1] += zn * qi;
+                }
+                acc[Q] += pi[v] * qi;
+                acc[Q + 1] += rn * rn;
             }
             i[v] = in[v];
             act[v] = an[v];
         }
     }
-    block_sum<2>(acc, lds);
-    if (threadIdx.x == 0) {
-        if (!MG) part[P_RZ * A.ldp + (int)blockIdx.x] = acc[0];   // MG: the V-cycle writes r.z
-        part[P_RR * A.ldp + (int)blockIdx.x] = acc[1];
-    }
+    // (MG: the V-cycle writes r.z, k_cg_dot (z, q))
+    tile_sum_to<MG ? 2 : 4>(acc, sum, part + (MG ? P_PQ : P_RZ) * A.ldp + (int)blockIdx.x, A.ldp);
 }
 
 // The scalars of iterate k for the host (one block); k = 0: b.b too.
@@ -543,7 +612,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_status(int ldp, int Gp, int k, do
         bb = reduce_parts(part + P_BB * ldp, Gp, lds);
         if (threadIdx.x == 0) scal[S_BB] = bb;
     }
-    cg_check(part + P_RR * ldp, Gp, k, bb, scal, lds);
+    cg_check(reduce_parts(part + P_RR * ldp, Gp, lds), k, bb, scal);
 }
 
 // The solution, rounded to the field storage; an odd number of iterations
@@ -718,7 +787,7 @@ __global__ __launch_bounds__(kBlock) void k_mg_res0(CgArgs A, int k, const doubl
     if (threadIdx.x < VG_NREG) cl[threadIdx.x] = A.c[threadIdx.x];
     if (!REG && threadIdx.x < 7) mtab[threadIdx.x] = 1.0 / (1.0 + A.a * (double)threadIdx.x);
     __syncthreads();
-    if (rr_part && cg_check(rr_part, Gp, k, scal[S_BB], scal, lds)) return;
+    if (rr_part && cg_check(reduce_parts(rr_part, Gp, lds), k, scal[S_BB], scal)) return;
     const int64_t nt = (A.n + kBlock * V - 1) / (kBlock * V);
     int64_t tl = xcd_stride_tile(blockIdx.x, gridDim.x, 0, nt, A.run);
     CgIdx<NS> i[V];
@@ -1189,7 +1258,8 @@ int cg_solve_t(vg_sim *h, int pool, double a, double rtol, int max_iter, int *it
         for (int it = 0; it < todo; it++) {
             const int k = launched + it;
             hipLaunchKernelGGL((k_cg_dot<REG, NS, MG, V>), dim3(Gd), dim3(kBlock), 0, s, A, k,
-                               MG ? mg_rz_blocks<REG, NS>(h) : (k > 0 ? Gs : Gi), (const double *)zb[k & 1], h->cg_scal, h->cg_part);
+                               MG ? mg_rz_blocks<REG, NS>(h) : (k > 0 ? Gs : Gi), Gs, (const double *)zb[k & 1],
+                               (const double *)h->cg_p[(k & 1) ^ 1], h->cg_scal, h->cg_part);
             if ((rc = launch_status("k_cg_dot"))) return rc;
             hipLaunchKernelGGL((k_cg_step<REG, NS, MG, V>), dim3(Gs), dim3(kBlock), 0, s, A, k, Gd,
                                (const double *)zb[k & 1], (const double *)h->cg_p[(k & 1) ^ 1], h->cg_p[k & 1], h->cg_y,

@@ -16,6 +16,8 @@ namespace vg {
 constexpr int kBlock = 256;          // threads per workgroup (4 wave64)
 constexpr int kWaves = kBlock / 64;
 constexpr int kNumXcd = 8;           // MI355X: 8 XCDs, 32 CUs each
+constexpr int kCgParts = 6;          // per-block sums the conjugate gradients keep
+constexpr int kCgScal = 16;          // their scalars
 
 // ---------------------------------------------------------------- errors
 void set_error(const char *fmt, ...);
@@ -171,8 +173,8 @@ __device__ inline double wave_sum(double v) {
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
-// Per-tile sums of M doubles written straight to out[0..M-1] in a fixed
-// order: each quad of lanes is reduced by DPP and one lane per quad stores
+// Per-tile sums of M doubles written straight to out[0], out[stride], ... in a
+// fixed order: each quad of lanes is reduced by DPP and one lane per quad stores
 // the quad sums in LDS; then the first wave adds, eight threads per value,
 // two 16-lane rows each (a row's quads as (q0 + q3) + (q2 + q1)) and the
 // eight pairs of rows pairwise by DPP.  `lds` must hold kQuads * M doubles;
@@ -183,7 +185,7 @@ __device__ inline double wave_sum(double v) {
 constexpr int kQuads = kBlock / 4;
 
 template <int M>
-__device__ inline void tile_sum_to(double (&v)[M], double *lds, double *__restrict__ out) {
+__device__ inline void tile_sum_to(double (&v)[M], double *lds, double *__restrict__ out, int stride = 1) {
     static_assert(M <= 8 && kQuads == 64, "eight threads of one wave per value");
 #pragma unroll
     for (int m = 0; m < M; m++) {
@@ -204,7 +206,7 @@ __device__ inline void tile_sum_to(double (&v)[M], double *lds, double *__restri
         x += dpp_move<0xB1>(x);
         x += dpp_move<0x4E>(x);
         x += dpp_move<0x141>(x);   // row_half_mirror: lane 7 - r of each eight
-        if (m < M && r == 0) out[m] = x;
+        if (m < M && r == 0) out[m * stride] = x;
     }
     __syncthreads();
 }
@@ -592,8 +594,8 @@ struct vg_sim {
     // implicit CG (FP64 vectors)
     double *cg_y = nullptr, *cg_r = nullptr, *cg_z = nullptr, *cg_m = nullptr;
     double *cg_p[2] = {nullptr, nullptr};
-    double *cg_part = nullptr;   // [4][cg_blocks]
-    double *cg_scal = nullptr;   // scalars (see vg_cg.hip)
+    double *cg_part = nullptr;   // [kCgParts][cg_blocks]
+    double *cg_scal = nullptr;   // [kCgScal] scalars (see vg_cg.hip)
     int cg_blocks = 0;
     // multigrid preconditioner of the CG (VG_FEAT_MG; vg_cg.hip).  Level 0 is
     // the pore voxels (the CG's own vectors); levels >= 1 are aggregates.
