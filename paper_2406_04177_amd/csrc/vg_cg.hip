@@ -18,8 +18,7 @@
 //    a 12^3 cube at a = 1e12 never converged and a chain of 400 at a = 1e6
 //    took 1.3 times the iterations.  The summed products keep the iteration
 //    counts of a directly summed (p, B p); beside the recurrence they cost an
-//    iteration 0.6 us (3 %) at 128^3, nothing measurable at 512^3, and the
-//    multigrid's 2 %.)
+//    iteration nothing measurable, and the multigrid's 2 % at 512^3.)
 //  - k_cg_step: p = z + beta p_old for the voxel and its neighbours, so that
 //    q = B p is formed in registers and never stored; z <- z - alpha M^-1 q
 //    into the other z buffer (r = M z is not stored: r_i is z_i times the
@@ -31,10 +30,12 @@
 // and updated x each time: 93.5 B; 512^3, 22.8 M voxels: see k_cg_step.)
 // There is no kernel for the scalars: each block of the kernel that needs
 // them adds up the partials of the kernel before it, in a fixed order, and
-// block 0 keeps the results for later kernels in slots no block of the same
-// kernel reads.  The host reads the scalars only every few iterations (the
-// number follows the convergence seen so far); kernels launched after
-// convergence return at once.
+// block 0 keeps the results for later kernels in slots no other block of the
+// same kernel reads.  That holds for the convergence flag too: the kernels
+// that check convergence do not look at it but repeat the check, whose
+// partials stay as they are once the flag is up; the others return on it at
+// once.  The host reads the scalars only every few iterations (the number
+// follows the convergence seen so far).
 //
 // Multigrid option (not in the paper, whose preconditioner is the diagonal):
 // M^-1 is one V-cycle over a hierarchy of aggregates.  Level l+1 has one cell
@@ -290,10 +291,10 @@ __device__ __forceinline__ double reduce_parts(const double *__restrict__ part, 
 }
 
 // Convergence of iterate k (k iterations done) from its r.r; block 0 keeps the
-// scalars.  True in every thread once converged.
+// scalars, once.  True in every thread of every block once converged.
 __device__ __forceinline__ bool cg_check(double rr, int k, double bb, double *__restrict__ scal) {
     const bool done = rr <= scal[S_RTOL2] * bb;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && scal[S_DONE] == 0.0) {
         scal[S_RR] = rr;
         scal[S_ITER] = (double)k;
         if (done) scal[S_DONE] = 1.0;
@@ -361,7 +362,7 @@ template <bool REG, int NS, bool MG, int V>
 __global__ __launch_bounds__(kBlock) void k_cg_dot(CgArgs A, int k, int Gp, int Gs, const double *__restrict__ z,
                                                    const double *__restrict__ pold, double *__restrict__ scal,
                                                    double *__restrict__ part) {
-    if (scal[S_DONE] != 0.0) return;
+    if (MG && scal[S_DONE] != 0.0) return;   // (Jacobi: this kernel's own check below)
     constexpr bool ST = V > 1;
     __shared__ double win[ST ? 2 : 1][ST ? kCgWin : 1];
     __shared__ double lds[kWaves * 3];
@@ -778,7 +779,7 @@ __global__ __launch_bounds__(kBlock) void k_mg_res0(CgArgs A, int k, const doubl
                                                     const double *__restrict__ m, double *__restrict__ t,
                                                     double *__restrict__ scal,
                                                     const double *__restrict__ rr_part, int Gp) {
-    if (scal[S_DONE] != 0.0) return;
+    if (!rr_part && scal[S_DONE] != 0.0) return;   // (with rr_part: this kernel's own check below)
     constexpr bool ST = V > 1;
     __shared__ double win[ST ? 2 : 1][ST ? kCgWin : 1];
     __shared__ double lds[kWaves];
