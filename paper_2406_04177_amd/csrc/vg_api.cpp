@@ -357,6 +357,15 @@ bool graphs_wanted(const vg_sim *h) {
     return h->n <= ((int64_t)1 << 19);   // measured: 1.35x at 48^3, 1.02x at 128^3, none from 256^3
 }
 
+// The band kernel's second field set holds the state only inside one call:
+// however the call ends (an odd number of pairs and then a failed launch,
+// too), later passes read the bound fields.
+struct BandRun {
+    vg_sim *h;
+    explicit BandRun(vg_sim *sim) : h(sim) { h->band_mid = 0; }
+    ~BandRun() { h->band_mid = 0; }
+};
+
 // Passes over slabs, for compensated fields.  Where they outgrow the 256 MB
 // last-level cache, consecutive passes run slab by slab: all passes of a
 // group on one slab of tiles (kSlabBytes of fields) before the next slab, so
@@ -580,6 +589,7 @@ extern "C" int vg_init_state(vg_sim *h, void *fields_d, void *alt_d, void *work_
     h->work = (char *)work_d;
     layout(h, h->work);
     h->cur = 0;
+    h->band_mid = 0;
     hipStream_t s = (hipStream_t)stream;
     int rc;
     if ((rc = hip_status(hipMemcpyAsync(h->piece_first, h->piece_first_h.data(), sizeof(int32_t) * h->piece_first_h.size(),
@@ -627,7 +637,7 @@ extern "C" int vg_step_explicit(vg_sim *h, int64_t nsteps, double dt, int64_t lo
     if ((rc = need_bound(h))) return rc;
     if (nsteps == 0 || h->n == 0) return VG_OK;
     hipStream_t s = (hipStream_t)stream;
-    h->band_mid = 0;
+    BandRun band_run(h);
     const size_t row = (size_t)h->nseg * 6;
     auto logged = [&](int64_t j) { return log_every > 0 && j % log_every == 0; };
     // the partials of up to tot_batch logged passes wait in their slots and

@@ -1379,6 +1379,10 @@ int dispatch(vg_sim *h, int mode, int tot, double dt_t, double dt_d, hipStream_t
         }
     }
     if (h->band_mid) {
+        if (mode != MODE_DT) {
+            set_error("only a fused pass takes the state back from the band kernel's field set");
+            return VG_ESTATE;
+        }
         const int rc = dispatch_bufs<R>(h, mode, tot, dt_t, dt_d, B, s);
         if (!rc) h->band_mid = 0;
         return rc;
