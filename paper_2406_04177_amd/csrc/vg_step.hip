@@ -1472,21 +1472,24 @@ int build_band(vg_sim *h, hipStream_t s) {
             if (!fits) continue;
             const size_t lds = h->prec == VG_F64 ? band_lds_bytes<double>(capf, cape) : band_lds_bytes<float>(capf, cape);
             if (lds > lds_max) continue;
+            // blocks resident at once (registers and this LDS size) on the
+            // device.  The attribute belongs to the kernel, not to the handle,
+            // so every handle sets the same value; a device that refuses it,
+            // or that holds no such block, gets single passes.
+            int per = 0, cus = 0, dev = 0;
+            const void *kern = h->prec == VG_F64 ? (const void *)k_band2<double> : (const void *)k_band2<float>;
+            if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_cu) != hipSuccess ||
+                hipGetDevice(&dev) != hipSuccess ||
+                hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+                hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, kBandThreads, lds) != hipSuccess ||
+                per < 1 || cus < 1) {
+                (void)hipGetLastError();
+                return VG_OK;
+            }
             h->band_h = H;
             h->band_capf = capf;
             h->band_cape = cape;
             h->band_nbands = (h->ny + H - 1) / H;
-            // blocks resident at once (registers and this LDS size) on the device
-            int per = 0, cus = 0, dev = 0;
-            const void *kern = h->prec == VG_F64 ? (const void *)k_band2<double> : (const void *)k_band2<float>;
-            if (lds > 64 * 1024) (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max);
-            if (hipGetDevice(&dev) != hipSuccess ||
-                hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-                hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, kBandThreads, lds) != hipSuccess || per < 1) {
-                (void)hipGetLastError();
-                per = 2;
-                cus = 256;
-            }
             const int chunks = std::max(1, std::min(per * cus / h->band_nbands, (h->nz + 3) / 4));
             h->band_z = (h->nz + chunks - 1) / chunks;
             h->band_ok = true;
