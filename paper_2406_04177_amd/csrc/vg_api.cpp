@@ -405,12 +405,12 @@ bool use_slabs(const vg_sim *h) {
     return (double)slab_skew(h) * kTile * kSlabPasses * bytes < 0.5 * kSlabBytes;
 }
 
-// The passes of a group (their totals in consecutive slots from the current one).
-int run_slabs(vg_sim *h, const std::vector<PassDesc> &group, hipStream_t s) {
-    const int T = (int)group.size(), cur0 = h->cur, slot0 = h->part_slot;
+// The T passes of a group (their totals in consecutive slots from the current one).
+int run_slabs(vg_sim *h, const PassDesc *group, int T, hipStream_t s) {
+    const int cur0 = h->cur, slot0 = h->part_slot;
     const int64_t skew = slab_skew(h), nt = h->ntiles;
     const int64_t slab = std::max<int64_t>(1, (int64_t)(kSlabBytes / pass_bytes_per_voxel(h) / kTile));
-    std::vector<int64_t> done((size_t)T, 0);
+    int64_t done[kSlabPasses] = {};
     int logged = 0, rc = VG_OK;
     for (int64_t q = 1; done[T - 1] < nt; q++) {
         const bool last = q * slab >= nt;
@@ -656,7 +656,8 @@ extern "C" int vg_step_explicit(vg_sim *h, int64_t nsteps, double dt, int64_t lo
         return flush();
     };
     if (use_slabs(h)) {
-        std::vector<PassDesc> group;
+        PassDesc group[kSlabPasses];   // no allocation: this is below a C entry
+        int size = 0, slots = 0;
         const bool td = h->params.step_order == VG_ORDER_TD;
         const int64_t npass = td ? nsteps + 1 : nsteps;
         for (int64_t q = 0; q < npass; q++) {
@@ -666,12 +667,11 @@ extern "C" int vg_step_explicit(vg_sim *h, int64_t nsteps, double dt, int64_t lo
             else if (td && q == nsteps) p = {MODE_D, logged(q) ? TOT_OUT : TOT_NONE, dt, dt};
             else if (td) p.tot = logged(q) ? TOT_MID : TOT_NONE;
             else p.tot = logged(q + 1) ? TOT_OUT : TOT_NONE;
-            group.push_back(p);
-            int slots = 0;
-            for (const PassDesc &g : group) slots += g.tot != TOT_NONE;
-            if ((int)group.size() == kSlabPasses || slots == h->tot_batch || q + 1 == npass) {
-                if ((rc = run_slabs(h, group, s))) return rc;
-                group.clear();
+            group[size++] = p;
+            slots += p.tot != TOT_NONE;
+            if (size == kSlabPasses || slots == h->tot_batch || q + 1 == npass) {
+                if ((rc = run_slabs(h, group, size, s))) return rc;
+                size = slots = 0;
                 if ((rc = flush())) return rc;
             }
         }

@@ -159,9 +159,35 @@ static void failed_runs() {
     }
 }
 
+// A step of compensated fields large enough for slabs allocates nothing: an
+// exception must not leave the C entry.
+static void no_allocation() {
+    vg_sim *h = make(7000000, VG_F32C);
+    size_t bytes = 0;
+    vg_workspace_bytes(h, &bytes);
+    char *work = (char *)std::calloc(1, bytes);
+    need(work != nullptr, "workspace");
+    bind(h, work, bytes);
+    h->xy_dist = 200;
+    h->z_dist = 10000;
+    std::vector<double> log(40 * 6);
+    for (int order : {VG_ORDER_TD, VG_ORDER_DT}) {
+        vg_params p = h->params;
+        p.step_order = order;
+        need(vg_set_params(h, &p) == VG_OK, "vg_set_params");
+        g_launches = 0;
+        g_no_alloc = true;
+        const int rc = vg_step_explicit(h, 37, 0.01, 3, log.data(), VG_FORCE, nullptr);
+        g_no_alloc = false;
+        need(rc == VG_OK, "step");
+        need(g_launches > 38, "the passes ran slab by slab");
+    }
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "failed_runs") failed_runs();
+    else if (what == "no_allocation") no_allocation();
     else need(false, "scenario name");
     std::printf("ok\n");
     return 0;

@@ -1,5 +1,5 @@
 """Scenarios of the C ABI's host side that a GPU does not bring about on
-demand (a launch that fails in the middle of a run): vg_api.cpp built for the
+demand (a launch that fails in the middle of a run, memory that runs out): vg_api.cpp built for the
 host alone, with stand-ins for the HIP calls and the kernel launchers
 (host_api_harness.cpp)."""
 import os
@@ -23,7 +23,7 @@ def harness(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["failed_runs"])
+@pytest.mark.parametrize("scenario", ["failed_runs", "no_allocation"])
 def test_scenario(harness, scenario):
     r = subprocess.run([harness, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout.endswith("ok\n"), r.stdout + r.stderr
