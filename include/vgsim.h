@@ -318,9 +318,10 @@ int vg_destroy(vg_sim *h);
  * fields once.  Needs the workspace of VG_FEAT_BAND and the relative codes;
  * used while only DOM diffuses, with unit edge weights (no region codes) and
  * Algorithm 1; other passes run on RELATIVE.  Bit-identical to RELATIVE.
- * AUTO takes BAND for FP32 and FP64 fields when it is available and the
- * volume has enough planes for chunks of at least 8 (about 300^3 and up in
- * FP32, 220^3 in FP64). */
+ * AUTO takes BAND for FP32 and FP64 fields when it is available, the volume
+ * has enough planes for chunks of at least 8 (about 300^3 and up in FP32, 220^3
+ * in FP64) and its own bytes promise a gain (not so where full rows leave bands
+ * of one or two rows, or most CUs idle). */
 #define VG_KERNEL_BAND     5
 int vg_set_kernel(vg_sim *h, int variant);
 

@@ -1430,12 +1430,33 @@ bool use_band(const vg_sim *h) {
 // FP32 twice (taller bands recompute fewer neighbour rows; a march step costs
 // about 3 us whatever its width, so lower ones only add steps); the chunks
 // are sized so that every block is resident at once.
-// AUTO takes the kernel where the chunks have at least 8 planes: shorter ones
-// spend too much on their two extra planes.  Measured, 33 steps, single
-// passes over pairs: FP32 chunks of 4-6 planes (200^3, 256^3) 0.69-1.03, 8-9
-// (300^3; 500x120x500) 1.07-1.19, 24 and more (420^3 and up) 1.40-1.47; FP64
-// 6 planes (200^3) 0.99, 10-18 (256^3, 300^3) 1.13-1.29, 28 and more
-// 1.59-1.66.
+// AUTO takes the kernel where two things hold.  The chunks have at least 8
+// planes: shorter ones spend too much on their two extra planes.  Measured, 33
+// steps, single passes over pairs: FP32 chunks of 4-6 planes (200^3, 256^3)
+// 0.69-1.03, 8-9 (300^3; 500x120x500) 1.07-1.20, 24 and more (420^3 and up)
+// 1.39-1.51; FP64 6 planes (200^3) 0.99, 10-18 (256^3, 300^3) 1.13-1.30, 28
+// and more 1.57-1.66.
+// And the single passes' bytes over the band kernel's own, times the share of
+// the resident blocks that its launch fills and the planes of a chunk over
+// those it marches, reach a break-even: where rows are full the slots leave
+// bands of one to three rows, whose pools are read (H + 2) / H times, and
+// their number may leave many CUs without a block.  Measured as above, with
+// that estimate in brackets, the fields larger than the last-level cache
+// (neighbour rows come from caches in part, so bands gain from 0.85 on):
+// 400x400x600 full FP32 0.82 [0.68], FP64 0.90 [0.69]; 300x300x800 at porosity
+// 0.4 FP64 0.85 [0.72]; 400^3 at 0.8 FP64 (134 blocks on 256 CUs) 0.92 [0.74],
+// full 1.02 [0.74]; 512^3 full FP64 1.08-1.14 [0.89]; 330x400x450 full FP32
+// 1.08 [0.94]; 450^3 at 0.8 1.15 [1.06], 1.26 [1.08]; 300^3 - 512^3 at 0.3 -
+// 0.7 1.34-1.79 [1.18 and more].  Within that cache single passes reread at
+// its rate: 120x120x1000 at 0.45 FP32 0.70 [0.77], 150x150x1000 at 0.35 FP32
+// 0.89-0.92 [1.00], 160x160x900 at 0.4 FP32 0.95-1.01 [1.07], 200x200x1000 at
+// 0.3 FP32 1.03-1.07 [1.14].  An FP32 block alone on its CU has too few loads
+// in flight: 20x512x512 full 0.87-0.90 [1.11], 300x480x500 at 0.9 0.97 [1.14],
+// 300x500x500 full 1.06 [1.18], 512^3 full 1.16 [1.22].
+// In FP32 one-row bands are not taken for the sake of two blocks on a CU (512^3
+// full: one row 1126 us a step, two rows 966, single passes 1123).
+constexpr double kBandGain = 0.85, kBandGainCached = 1.05, kBandGainAlone = 1.15, kBandCached = 256e6;
+
 int build_band(vg_sim *h, hipStream_t s) {
     h->band_ok = false;
     h->band_auto = false;
@@ -1454,7 +1475,7 @@ int build_band(vg_sim *h, hipStream_t s) {
     static const int hs[] = {32, 28, 24, 20, 18, 16, 14, 12, 11, 10, 9, 8, 7, 6, 5, 4, 3, 2, 1};
     for (size_t lds_max = h->prec == VG_F64 ? lds_cu : lds_cu / 2; lds_max <= lds_cu; lds_max *= 2) {
         for (int H : hs) {
-            int64_t capf = 1, cape = 1;
+            int64_t capf = 1, cape = 1, sumf = 0, sume = 0;   // widest ranges and sums over the bands and planes
             bool fits = true;
             for (int z = 0; z < h->nz && fits; z++)
                 for (int y0 = 0; y0 < h->ny; y0 += H) {
@@ -1464,6 +1485,8 @@ int build_band(vg_sim *h, hipStream_t s) {
                     const int64_t f = (int64_t)row[std::min(y1 + 2, h->ny)] - row[std::max(y0 - 2, 0)];
                     capf = std::max(capf, f);
                     cape = std::max(cape, ee - es);
+                    sumf += f;
+                    sume += ee - es;
                     if (ee - es / kGroup * kGroup > kBandSlots || f > (int64_t)kBandThreads * kBandRaw) {
                         fits = false;
                         break;
@@ -1471,7 +1494,7 @@ int build_band(vg_sim *h, hipStream_t s) {
                 }
             if (!fits) continue;
             const size_t lds = h->prec == VG_F64 ? band_lds_bytes<double>(capf, cape) : band_lds_bytes<float>(capf, cape);
-            if (lds > lds_max) continue;
+            if (lds > lds_max || (H < 2 && lds_max < lds_cu)) continue;
             // blocks resident at once (registers and this LDS size) on the
             // device.  The attribute belongs to the kernel, not to the handle,
             // so every handle sets the same value; a device that refuses it,
@@ -1493,7 +1516,20 @@ int build_band(vg_sim *h, hipStream_t s) {
             const int chunks = std::max(1, std::min(per * cus / h->band_nbands, (h->nz + 3) / 4));
             h->band_z = (h->nz + chunks - 1) / chunks;
             h->band_ok = true;
-            h->band_auto = h->band_z >= 8;
+            // bytes of two passes: DOM of the f ranges, the other pools and the codes of the e ranges, the output;
+            // against two single passes
+            const double R = (double)h->elem(), codes = 4.5, n = (double)h->n;
+            const double pair = R * (double)sumf + (4.0 * R + codes) * (double)sume + 5.0 * R * n;
+            const double singles = 2.0 * (10.0 * R + codes) * n;
+            const int64_t resident = (int64_t)per * cus;
+            const int64_t blocks = (int64_t)h->band_nbands * ((h->nz + h->band_z - 1) / h->band_z);
+            const int64_t rounds = (blocks + resident - 1) / resident;
+            const double filled = (double)blocks / (double)(rounds * resident);
+            const double planes = (double)h->band_z / (double)(h->band_z + 2);
+            const double gain = h->prec == VG_F32 && per == 1 ? kBandGainAlone
+                                : 5.0 * R * n <= kBandCached  ? kBandGainCached
+                                                              : kBandGain;
+            h->band_auto = h->band_z >= 8 && filled * planes * singles >= gain * pair;
             return VG_OK;
         }
     }
