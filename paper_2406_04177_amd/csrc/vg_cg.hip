@@ -127,7 +127,10 @@ struct CgArgs {
 
 // Neighbour sources of the CG kernels (the explicit step's): the table, or
 // a packed source; an absent neighbour comes back as the voxel itself.
-enum { NS_TABLE = 0, NS_REL = 1, NS_OFF = 2 };
+// NS_WIDE: a packed source whose FP64 vectors outgrow 32-bit byte offsets.
+enum { NS_TABLE = 0, NS_REL = 1, NS_OFF = 2, NS_WIDE = 4 };
+template <int NS>
+constexpr bool kRel = (NS & ~NS_WIDE) == NS_REL;
 
 template <int NS>
 __device__ __forceinline__ void cg_neighbours(const CgArgs &A, int64_t i, int64_t (&j)[6], bool (&pres)[6]) {
@@ -140,8 +143,8 @@ __device__ __forceinline__ void cg_neighbours(const CgArgs &A, int64_t i, int64_
         }
     } else {
         uint32_t jp[6];
-        const PackedWords W = packed_words<NS == NS_REL>(A.pk, (uint32_t)i);
-        packed_decode<NS == NS_REL>(A.pk, (uint32_t)i, W, jp);
+        const PackedWords W = packed_words<kRel<NS>>(A.pk, (uint32_t)i);
+        packed_decode<kRel<NS>>(A.pk, (uint32_t)i, W, jp);
 #pragma unroll
         for (int k = 0; k < 6; k++) {
             j[k] = (int64_t)jp[k];
@@ -151,10 +154,10 @@ __device__ __forceinline__ void cg_neighbours(const CgArgs &A, int64_t i, int64_
 }
 
 // Index type: 32 bits with a packed source (one address register per lane
-// beside the array's base; the host takes the table where n doubles do not
-// fit 2^32 bytes), 64 with the table.
+// beside the array's base), 64 where n doubles do not fit 2^32 bytes and with
+// the table.
 template <int NS>
-using CgIdx = std::conditional_t<NS == NS_TABLE, int64_t, uint32_t>;
+using CgIdx = std::conditional_t<NS == NS_TABLE || (NS & NS_WIDE) != 0, int64_t, uint32_t>;
 template <typename T>
 __device__ __forceinline__ T &el(T *b, uint32_t i) {
     return at(b, i);
@@ -171,7 +174,7 @@ template <int NS>
 struct CgWords {
     int32_t jt[NS == NS_TABLE ? 6 : 1];
     PackedWords W;
-    uint32_t base[NS == NS_REL ? 6 : 1];
+    uint32_t base[kRel<NS> ? 6 : 1];
 };
 
 template <int NS>
@@ -181,8 +184,8 @@ __device__ __forceinline__ void cg_words(const CgArgs &A, CgIdx<NS> i, CgWords<N
 #pragma unroll
         for (int k = 0; k < 6; k++) w.jt[k] = A.nbr[(int64_t)k * A.n + i];
     } else {
-        w.W = packed_words<NS == NS_REL>(A.pk, (uint32_t)i);
-        if constexpr (NS == NS_REL) {
+        w.W = packed_words<kRel<NS>>(A.pk, (uint32_t)i);
+        if constexpr (kRel<NS>) {
             const uint32_t grp = __builtin_amdgcn_readfirstlane((uint32_t)i / (uint32_t)kGroup);
             const uint32_t *bp = A.pk.rel_base + (size_t)grp * 8;
 #pragma unroll
@@ -201,12 +204,13 @@ __device__ __forceinline__ void cg_decode(const CgArgs &A, CgIdx<NS> i, const Cg
             pres[k] = w.jt[k] >= 0;
             j[k] = pres[k] ? (int64_t)w.jt[k] : i;
         }
-    } else if constexpr (NS == NS_REL) {
+    } else if constexpr (kRel<NS>) {
+        const uint32_t u = (uint32_t)i;
 #pragma unroll
         for (int k = 0; k < 6; k++) {
             const uint32_t c = (w.W.a >> A.pk.rl.sh[k]) & A.pk.rl.mk[k];
             const uint32_t d = w.base[k] + (c ? c - 1u : 0u), last = (uint32_t)A.n - 1u;
-            j[k] = (k & 1) ? min(i + d, last) : i - min(d, i);
+            j[k] = (CgIdx<NS>)((k & 1) ? min(u + d, last) : u - min(d, u));
             pres[k] = c != 0;
         }
     } else {
@@ -214,7 +218,7 @@ __device__ __forceinline__ void cg_decode(const CgArgs &A, CgIdx<NS> i, const Cg
         packed_decode<false>(A.pk, (uint32_t)i, w.W, jp);
 #pragma unroll
         for (int k = 0; k < 6; k++) {
-            j[k] = jp[k];
+            j[k] = (CgIdx<NS>)jp[k];
             pres[k] = j[k] != i;
         }
     }
@@ -1313,9 +1317,11 @@ int mg_apply_ns(vg_sim *h, double a, const double *r, double *z, hipStream_t s) 
                : mg_vcycle<false, NS, V>(h, A, 0, 0, r, h->cg_m, z, s);
 }
 
-// The explicit step's neighbour source, but the table where the FP64 vectors
-// outgrow the packed sources' 32-bit byte offsets (the fields may be FP32).
-bool cg_packed(const vg_sim *h) { return (uint64_t)h->n * sizeof(double) < ((uint64_t)1 << 32); }
+// The FP64 vectors outgrow 32-bit byte offsets.  (A packed source then means
+// FP32 fields of 2^29 voxels and more: their codes still fit, and the table
+// reads 24 B per voxel and kernel for the codes' 4.5.  560 M voxels: 16.9 ms
+// an iteration with the table, 13.8 with codes and 64-bit indices.)
+bool cg_wide(const vg_sim *h) { return (uint64_t)h->n * sizeof(double) >= ((uint64_t)1 << 32); }
 
 // The staged kernels: relative codes, x and y distances within the halo, and
 // enough voxels (see kCgTileV).
@@ -1326,7 +1332,13 @@ bool cg_staged(const vg_sim *h) {
 template <typename F>
 int cg_solve(vg_sim *h, int pool, double a, double rtol, int max_iter, int *iters, double *relres,
              hipStream_t s) {
-    if (!cg_packed(h)) return cg_solve_ns<F, NS_TABLE, 1>(h, pool, a, rtol, max_iter, iters, relres, s);
+    if (cg_wide(h)) {
+        if constexpr (!std::is_same_v<F, PlainAcc<double>>) {
+            if (use_relative(h)) return cg_solve_ns<F, NS_REL | NS_WIDE, 1>(h, pool, a, rtol, max_iter, iters, relres, s);
+            if (use_offsets(h)) return cg_solve_ns<F, NS_OFF | NS_WIDE, 1>(h, pool, a, rtol, max_iter, iters, relres, s);
+        }
+        return cg_solve_ns<F, NS_TABLE, 1>(h, pool, a, rtol, max_iter, iters, relres, s);
+    }
     if (cg_staged(h)) return cg_solve_ns<F, NS_REL, kCgTileV>(h, pool, a, rtol, max_iter, iters, relres, s);
     if (use_relative(h)) return cg_solve_ns<F, NS_REL, 1>(h, pool, a, rtol, max_iter, iters, relres, s);
     if (use_offsets(h)) return cg_solve_ns<F, NS_OFF, 1>(h, pool, a, rtol, max_iter, iters, relres, s);
@@ -1395,7 +1407,11 @@ int mg_build(vg_sim *h, hipStream_t s) {
 
 int mg_apply(vg_sim *h, double a, const double *r, double *z, hipStream_t s) {
     if (h->n == 0) return VG_OK;
-    if (!cg_packed(h)) return mg_apply_ns<NS_TABLE, 1>(h, a, r, z, s);
+    if (cg_wide(h)) {
+        if (use_relative(h)) return mg_apply_ns<NS_REL | NS_WIDE, 1>(h, a, r, z, s);
+        if (use_offsets(h)) return mg_apply_ns<NS_OFF | NS_WIDE, 1>(h, a, r, z, s);
+        return mg_apply_ns<NS_TABLE, 1>(h, a, r, z, s);
+    }
     if (cg_staged(h)) return mg_apply_ns<NS_REL, kCgTileV>(h, a, r, z, s);
     if (use_relative(h)) return mg_apply_ns<NS_REL, 1>(h, a, r, z, s);
     if (use_offsets(h)) return mg_apply_ns<NS_OFF, 1>(h, a, r, z, s);
