@@ -89,8 +89,8 @@ static_assert(S_NSCAL <= kCgScal && P_N == kCgParts, "the workspace layout's siz
 // consecutive voxels and a halo of kCgHalo voxels on each side into LDS by
 // contiguous loads, reads the x and y neighbours there (4 cycles per wave)
 // and gathers only the z neighbours; it needs the x and y distances to fit
-// the halo, and enough voxels that every CU has tiles (kCgStagedMin).  The
-// direct form, one voxel per thread, serves the rest.
+// the halo, enough voxels that every CU has tiles (kCgStagedMin) and unit
+// weights (cg_staged).  The direct form, one voxel per thread, serves the rest.
 constexpr int kCgTileV = 4;
 constexpr int kMgPostV = 2;      // voxels per thread of the V-cycle's last kernel
 constexpr int kCgHalo = 256;
@@ -1288,10 +1288,11 @@ int cg_solve_t(vg_sim *h, int pool, double a, double rtol, int max_iter, int *it
 template <typename F, int NS, int V>
 int cg_solve_ns(vg_sim *h, int pool, double a, double rtol, int max_iter, int *iters, double *relres,
                 hipStream_t s) {
-    const bool reg = h->rcode != nullptr;
     const bool mg = h->precond == VG_PRECOND_MG && h->mg_levels >= 2;
-    if (reg) return mg ? cg_solve_t<F, NS, true, true, V>(h, pool, a, rtol, max_iter, iters, relres, s)
-                       : cg_solve_t<F, NS, true, false, V>(h, pool, a, rtol, max_iter, iters, relres, s);
+    if constexpr (V == 1) {   // (staged: unit weights, see cg_staged)
+        if (h->rcode) return mg ? cg_solve_t<F, NS, true, true, V>(h, pool, a, rtol, max_iter, iters, relres, s)
+                                : cg_solve_t<F, NS, true, false, V>(h, pool, a, rtol, max_iter, iters, relres, s);
+    }
     return mg ? cg_solve_t<F, NS, false, true, V>(h, pool, a, rtol, max_iter, iters, relres, s)
               : cg_solve_t<F, NS, false, false, V>(h, pool, a, rtol, max_iter, iters, relres, s);
 }
@@ -1313,8 +1314,10 @@ int mg_apply_ns(vg_sim *h, double a, const double *r, double *z, hipStream_t s) 
     // the V-cycle's kernels check the convergence flag: clear it
     if ((rc = hip_status(hipMemsetAsync(h->cg_scal, 0, sizeof(double) * S_NSCAL, s), "cg scalars"))) return rc;
     if ((rc = mg_prepare(h, a, s))) return rc;
-    return reg ? mg_vcycle<true, NS, V>(h, A, 0, 0, r, h->cg_m, z, s)
-               : mg_vcycle<false, NS, V>(h, A, 0, 0, r, h->cg_m, z, s);
+    if constexpr (V == 1) {
+        if (reg) return mg_vcycle<true, NS, V>(h, A, 0, 0, r, h->cg_m, z, s);
+    }
+    return mg_vcycle<false, NS, V>(h, A, 0, 0, r, h->cg_m, z, s);
 }
 
 // The FP64 vectors outgrow 32-bit byte offsets.  (A packed source then means
@@ -1323,10 +1326,14 @@ int mg_apply_ns(vg_sim *h, double a, const double *r, double *z, hipStream_t s) 
 // an iteration with the table, 13.8 with codes and 64-bit indices.)
 bool cg_wide(const vg_sim *h) { return (uint64_t)h->n * sizeof(double) >= ((uint64_t)1 << 32); }
 
-// The staged kernels: relative codes, x and y distances within the halo, and
-// enough voxels (see kCgTileV).
+// The staged kernels: relative codes, x and y distances within the halo,
+// enough voxels (see kCgTileV) and unit weights.  Measured, 16 iterations,
+// direct over staged: unit weights 1 - 2 M voxels 0.97-1.20, 4 M and more
+// 1.00-1.35 (Jacobi), 0.99-1.15 (multigrid); with region weights, whose table
+// reads the registers of four voxels leave no waves to hide, 0.76-0.93 and
+// 0.84-0.89 at every size from 1 to 16 M.
 bool cg_staged(const vg_sim *h) {
-    return use_relative(h) && h->xy_dist >= 0 && h->xy_dist <= kCgHalo && h->n >= kCgStagedMin;
+    return use_relative(h) && !h->rcode && h->xy_dist >= 0 && h->xy_dist <= kCgHalo && h->n >= kCgStagedMin;
 }
 
 template <typename F>
