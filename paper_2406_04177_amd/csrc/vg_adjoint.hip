@@ -704,20 +704,28 @@ __global__ __launch_bounds__(kBlock) void k_fill_i32(int32_t *__restrict__ p, in
 
 // Voxels per thread of the staged kernel, and where it runs: FP32 (in FP64
 // its registers leave two waves on a SIMD), relative codes whose x and y
-// distances fit a halo of at most a block, enough voxels to give every CU
-// tiles, and not region weights without the static pools' D (one gathered
-// pool: the region sums bound it either way).  Measured, gradient calls with
-// k_adj over the staged kernel: 4.4 M voxels, every D 1.07 (unit weights) and
-// 1.04 (regions), DOM's D only 1.01 and 0.95; FP64 0.98-1.07; 22.8 M voxels
-// 1.07; below 1 M voxels 1.00-1.01.
+// distances fit a halo of at most a block, and not region weights without the
+// static pools' D (one gathered pool: the region sums bound it either way).
+// And enough voxels.  Where every group's neighbours lie at one distance (full
+// rows, codes of one bit) the direct kernel's gathers are contiguous loads too,
+// so that staging only pays far beyond the caches.  Measured, reverse sweeps of
+// six steps, direct over staged, states / kept DOM:
+//   DOM's D only: 1.1 - 1.7 M voxels 0.96-1.02, 2.0 - 2.4 M 1.01-1.09, more
+//   1.00-1.12; full rows 2.1 M 1.04 / 1.01, 8 M 1.10;
+//   every D: 1.1 - 1.7 M 0.97-1.05, 2.0 - 4.2 M 1.01-1.12, more 1.10-1.27; full
+//   rows 1.2 - 4.1 M 0.85-1.01, 8 M 1.05 / 1.03, 16 M 1.14 / 1.11;
+//   every D, regions: 1.1 - 1.7 M 0.92-1.01, 2.0 - 4.2 M 0.96-1.06, more
+//   1.01-1.17; full rows 1.2 - 4.1 M 0.84-0.92, 8 M 0.97 / 0.93, 16 M 1.06 / 1.01;
+//   FP64 0.98-1.07.
 template <bool DALL>
 constexpr int kAdjV = DALL ? 2 : 4;
-constexpr int64_t kAdjStagedMin = (int64_t)1 << 20;
 
 template <typename R, bool REG, bool DALL>
 bool adj_staged(const vg_sim *h) {
-    return sizeof(R) == sizeof(float) && (!REG || DALL) && h->xy_dist >= 0 && h->xy_dist <= kBlock &&
-           h->n >= kAdjStagedMin;
+    if (sizeof(R) != sizeof(float) || (REG && !DALL) || h->xy_dist < 0 || h->xy_dist > kBlock) return false;
+    const bool full = DALL && h->rel_layout.mk[2] <= 1u && h->rel_layout.mk[4] <= 1u;
+    const int64_t unit = (int64_t)1 << 20;
+    return h->n >= (full ? (REG ? 12 * unit : 6 * unit) : (REG || !DALL ? 2 * unit : unit));
 }
 
 template <typename R, bool REG, bool DALL>
