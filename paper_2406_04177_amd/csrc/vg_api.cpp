@@ -378,12 +378,18 @@ struct BandRun {
 // Measured at 512^3 (64.5 B per voxel and pass, 10 steps): whole passes 3.44
 // ms; slabs of 64, 96, 128, 192 MB 3.32, 3.01, 2.90 and 2.95 ms, with runs of
 // an eighth of a plane 2.84-2.97.  A launch's start and end cost about 5 us, so
-// smaller slabs lose (32 MB 4.15 ms), as do fields that fit the cache.
+// smaller slabs lose (32 MB 4.15 ms), as do fields little larger than the cache
+// (whole passes over slabs, runs of 2 - 33 passes: 262 MB 0.87-0.96, 328 MB
+// 0.94-1.12) and short runs: the first pass still reads memory.  At 328 MB - 2.7
+// GB 2 passes 0.92-0.97, 3 0.96-1.00, 4 0.99-1.05, 17 1.09-1.19 where only DOM
+// diffuses (groups of 3 inside a longer run 1.03); 2 passes 1.01-1.07 where all
+// pools do.
 // (Plain fields on single passes, as with region weights, gained 1.04-1.16,
 // but the range cost a 48^3 pass 3 %, and a second instance of every pass is
 // not worth it.)
-constexpr double kSlabBytes = 192e6, kSlabMinBytes = 256e6;
+constexpr double kSlabBytes = 192e6, kSlabMinBytes = 300e6;
 constexpr int kSlabPasses = 16;      // passes of a group
+constexpr int kSlabGroupMin = 3, kSlabRunMin = 4;   // fewer (2 where all pools diffuse): whole passes
 
 struct PassDesc {
     int mode, tot;
@@ -403,6 +409,17 @@ bool use_slabs(const vg_sim *h) {
     const double bytes = pass_bytes_per_voxel(h);
     if ((double)h->n * bytes < kSlabMinBytes) return false;
     return (double)slab_skew(h) * kTile * kSlabPasses * bytes < 0.5 * kSlabBytes;
+}
+
+// The T passes of a group as whole passes (totals as in run_slabs).
+int run_whole(vg_sim *h, const PassDesc *group, int T, hipStream_t s) {
+    for (int k = 0; k < T; k++) {
+        const PassDesc &p = group[k];
+        const int rc = launch_pass2(h, p.mode, p.tot, p.dt_t, p.dt_d, s);
+        if (rc) return rc;
+        if (p.tot != TOT_NONE) h->part_slot++;
+    }
+    return VG_OK;
 }
 
 // The T passes of a group (their totals in consecutive slots from the current one).
@@ -670,7 +687,9 @@ extern "C" int vg_step_explicit(vg_sim *h, int64_t nsteps, double dt, int64_t lo
             group[size++] = p;
             slots += p.tot != TOT_NONE;
             if (size == kSlabPasses || slots == h->tot_batch || q + 1 == npass) {
-                if ((rc = run_slabs(h, group, size, s))) return rc;
+                const bool slabs = size >= (h->mobile_all ? 2 : kSlabGroupMin) &&
+                                   npass >= (h->mobile_all ? 2 : kSlabRunMin);
+                if ((rc = slabs ? run_slabs(h, group, size, s) : run_whole(h, group, size, s))) return rc;
                 size = slots = 0;
                 if ((rc = flush())) return rc;
             }

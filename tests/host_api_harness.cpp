@@ -162,7 +162,7 @@ static void failed_runs() {
 // A step of compensated fields large enough for slabs allocates nothing: an
 // exception must not leave the C entry.
 static void no_allocation() {
-    vg_sim *h = make(7000000, VG_F32C);
+    vg_sim *h = make(8000000, VG_F32C);
     size_t bytes = 0;
     vg_workspace_bytes(h, &bytes);
     char *work = (char *)std::calloc(1, bytes);
@@ -184,10 +184,34 @@ static void no_allocation() {
     }
 }
 
+// Runs of fewer than four passes gain nothing from slabs: one launch a pass;
+// so do fields little larger than the last-level cache.
+static void short_runs() {
+    struct Run {
+        int64_t n, steps, launches;   // launches 0: slab by slab
+    };
+    for (const Run &r : {Run{8000000, 1, 2}, Run{8000000, 2, 3}, Run{8000000, 3, 0}, Run{7000000, 12, 13}}) {
+        vg_sim *h = make(r.n, VG_F32C);
+        size_t bytes = 0;
+        vg_workspace_bytes(h, &bytes);
+        char *work = (char *)std::calloc(1, bytes);
+        need(work != nullptr, "workspace");
+        bind(h, work, bytes);
+        h->xy_dist = 200;
+        h->z_dist = 10000;
+        g_launches = 0;
+        need(vg_step_explicit(h, r.steps, 0.01, 0, nullptr, VG_FORCE, nullptr) == VG_OK, "step");
+        need(r.launches ? g_launches == r.launches : g_launches > r.steps + 1, "launches of the run");
+        vg_destroy(h);
+        std::free(work);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "failed_runs") failed_runs();
     else if (what == "no_allocation") no_allocation();
+    else if (what == "short_runs") short_runs();
     else need(false, "scenario name");
     std::printf("ok\n");
     return 0;

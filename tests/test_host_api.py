@@ -23,7 +23,7 @@ def harness(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["failed_runs", "no_allocation"])
+@pytest.mark.parametrize("scenario", ["failed_runs", "no_allocation", "short_runs"])
 def test_scenario(harness, scenario):
     r = subprocess.run([harness, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout.endswith("ok\n"), r.stdout + r.stderr
