@@ -17,8 +17,8 @@
 //    Appl. Math. 25, 1989 - but rounding loses it on ill-conditioned systems:
 //    a 12^3 cube at a = 1e12 never converged and a chain of 400 at a = 1e6
 //    took 1.3 times the iterations.  The summed products keep the iteration
-//    counts of a directly summed (p, B p); beside the recurrence they cost an
-//    iteration nothing measurable, and the multigrid's 2 % at 512^3.)
+//    counts of a directly summed (p, B p), and cost nothing measurable beside
+//    the recurrence.)
 //  - k_cg_step: p = z + beta p_old for the voxel and its neighbours, so that
 //    q = B p is formed in registers and never stored; z <- z - alpha M^-1 q
 //    into the other z buffer (r = M z is not stored: r_i is z_i times the
@@ -53,18 +53,20 @@
 // than its diagonal).  The restriction is computed per coarse cell from its
 // children (found with the level's rank index in a fixed order) and the
 // prolongation per fine cell from its parent, so no sum depends on
-// scheduling.  Every level's kernels are one thread per cell: residual,
-// restriction (sum over the children), then prolongation and post-smoothing
-// in one.  With t = r - B x the residual of the pre-smoothed x, and P e the
+// scheduling.  Three kernels per level: residual, restriction (sum over the
+// children), then prolongation and post-smoothing in one; one thread per cell,
+// the fine level's residual and last kernel in grid strides of several voxels.  With t = r - B x the residual of the pre-smoothed x, and P e the
 // prolongated coarse solution, the post-smoothed result is
 //   y + w D^-1 (r - B y) = x + P e + w D^-1 (t - B P e),  y = x + P e,
 // and P e is constant on every 2x2x2 block: of a cell's six neighbours three
 // lie in its own block (their terms vanish) and the others in the three
 // coarse neighbours on its side, so this kernel gathers only from the four
 // times smaller coarse solution.  With the multigrid r is kept (in place of
-// the z update: 28.5 B read by k_cg_step), the V-cycle writes z and the r.z
-// partials, and k_cg_dot, which has B z in registers, sums (z, q_old) as
-// (B z, p_old) (20.5 B).
+// the z update: 28.5 B read by k_cg_step) and the V-cycle writes z and the r.z
+// partials.  z comes after the step that holds q_old, but the V-cycle M^-1 is
+// symmetric: (z, q_old) = (z, r_old - r) / alpha_old, and (z, r_old) =
+// (r, z_old), which that step sums.  (As (B z, p_old) in k_cg_dot it took
+// another vector's stream, 2 % of a solve.)
 #include <type_traits>
 
 #include "vg_internal.h"
@@ -77,8 +79,9 @@ namespace {
 // iterations done, the squared tolerance, and (p, q) and (z, q) of the
 // iteration before (z the one after it).
 enum { S_RZ = 0, S_ALPHA = 2, S_RR = 4, S_BB, S_DONE, S_ITER, S_RTOL2, S_PQ, S_ZQ, S_NSCAL };
-// Partials per block, one array of CgArgs::ldp each: r.z, (z, q), (p, q),
-// r.r (k_cg_step's, in this order), b.b, z.Bz.
+// Partials per block, one array of CgArgs::ldp each: r.z, (z, q) (MG: (r, z) of
+// the new r and the old z), (p, q), r.r (k_cg_step's, in this order), b.b,
+// z.Bz.
 enum { P_RZ = 0, P_ZQ, P_PQ, P_RR, P_BB, P_ZBZ, P_N };
 static_assert(S_NSCAL <= kCgScal && P_N == kCgParts, "the workspace layout's sizes");
 
@@ -354,18 +357,16 @@ __global__ __launch_bounds__(kBlock) void k_cg_init(CgArgs A, F field, double *_
     }
 }
 
-// Partials of (z, B z) of iteration k (MG: and of (B z, p_old)); before that
-// r.z of iterate k from its Gp partials, (p, q) and (z, q) of the iteration
-// before from its Gs, and for Jacobi the convergence check (the V-cycle has
-// done it).
+// Partials of (z, B z) of iteration k; before that r.z of iterate k from its
+// Gp partials, (p, q) and (z, q) of the iteration before from its Gs, and for
+// Jacobi the convergence check (the V-cycle has done it).
 // In every gathering kernel a tile's neighbour words are loaded one tile
 // ahead, so that its gathers wait for nothing; the staged window is double
 // buffered (one barrier per tile).
 // 512^3 (22.8 M voxels): 125 us direct, 92 us staged (12.5 B per voxel).
 template <bool REG, int NS, bool MG, int V>
 __global__ __launch_bounds__(kBlock) void k_cg_dot(CgArgs A, int k, int Gp, int Gs, const double *__restrict__ z,
-                                                   const double *__restrict__ pold, double *__restrict__ scal,
-                                                   double *__restrict__ part) {
+                                                   double *__restrict__ scal, double *__restrict__ part) {
     if (MG && scal[S_DONE] != 0.0) return;   // (Jacobi: this kernel's own check below)
     constexpr bool ST = V > 1;
     __shared__ double win[ST ? 2 : 1][ST ? kCgWin : 1];
@@ -378,19 +379,18 @@ __global__ __launch_bounds__(kBlock) void k_cg_dot(CgArgs A, int k, int Gp, int 
     // (p, q) hold nothing and are not used)
     if (blockIdx.x == 0) {
         const double *const p[3] = {part + P_RZ * A.ldp, part + P_ZQ * A.ldp, part + P_PQ * A.ldp};
-        const int G[3] = {Gp, MG || k == 0 ? 0 : Gs, k == 0 ? 0 : Gs};
+        const int Gq = k == 0 ? 0 : Gs, G[3] = {Gp, Gq, Gq};
         double v[3];
         reduce_parts<3>(p, G, lds, v);
         if (threadIdx.x == 0) {
             scal[S_RZ + (k & 1)] = v[0];
-            scal[S_ZQ] = v[1];
+            scal[S_ZQ] = MG ? (v[1] - v[0]) / scal[S_ALPHA + ((k & 1) ^ 1)] : v[1];
             scal[S_PQ] = v[2];
         }
     }
     if (!MG && cg_check(reduce_parts(part + P_RR * A.ldp, Gp, lds), k, scal[S_BB], scal)) return;
-    const bool first = k == 0;   // p_old holds nothing before the first direction
     const int64_t nt = (A.n + kBlock * V - 1) / (kBlock * V);
-    double acc[MG ? 2 : 1] = {};
+    double acc[1] = {0.0};
     int64_t t = xcd_stride_tile(blockIdx.x, gridDim.x, 0, nt, A.run);
     CgIdx<NS> i[V];
     bool act[V];
@@ -401,7 +401,6 @@ __global__ __launch_bounds__(kBlock) void k_cg_dot(CgArgs A, int k, int Gp, int 
     for (int64_t it = 1; t < nt; it++) {
         bool pres[V][6];
         double zi[V], zj[V][6];
-        [[maybe_unused]] double po[V];
         [[maybe_unused]] uint32_t q[V][4];
         [[maybe_unused]] double hz[2];
 #pragma unroll
@@ -409,7 +408,6 @@ __global__ __launch_bounds__(kBlock) void k_cg_dot(CgArgs A, int k, int Gp, int 
             CgIdx<NS> j[6];
             cg_decode<NS>(A, i[v], w[v], j, pres[v]);
             zi[v] = el(z, i[v]);
-            if constexpr (MG) po[v] = first ? 0.0 : el(pold, i[v]);
 #pragma unroll
             for (int k6 = ST ? 4 : 0; k6 < 6; k6++) zj[v][k6] = el(z, j[k6]);
             if constexpr (ST) {
@@ -445,21 +443,16 @@ __global__ __launch_bounds__(kBlock) void k_cg_dot(CgArgs A, int k, int Gp, int 
                 const double wt = weight(A.rcode, cl, i[v], k6, REG);
                 s += pres[v][k6] ? wt * (zi[v] - zj[v][k6]) : 0.0;
             }
-            const double bz = zi[v] + A.a * s;
-            acc[0] += act[v] ? zi[v] * bz : 0.0;
-            if constexpr (MG) acc[1] += act[v] ? po[v] * bz : 0.0;
+            acc[0] += act[v] ? zi[v] * (zi[v] + A.a * s) : 0.0;
             i[v] = in[v];
             act[v] = an[v];
         }
     }
-    block_sum<MG ? 2 : 1>(acc, lds);
-    if (threadIdx.x == 0) {
-        part[P_ZBZ * A.ldp + (int)blockIdx.x] = acc[0];
-        if constexpr (MG) part[P_ZQ * A.ldp + (int)blockIdx.x] = acc[1];
-    }
+    block_sum<1>(acc, lds);
+    if (threadIdx.x == 0) part[P_ZBZ * A.ldp + (int)blockIdx.x] = acc[0];
 }
 
-// Iteration k's update: alpha and beta from the Gp partials of (z, B z) (MG: and (z, q_old)),
+// Iteration k's update: alpha and beta from the Gp partials of (z, B z),
 // p = z + beta p_old (for the neighbours too), q = B p, then z' = z - alpha
 // M^-1 q (Jacobi, into zr) or r -= alpha q (MG, zr in place).  Odd k also add
 // the last two directions to y.  512^3: 325 us direct, 255 us staged (44.5 B
@@ -474,28 +467,17 @@ __global__ __launch_bounds__(kBlock) void k_cg_step(CgArgs A, int k, int Gp, con
     constexpr bool ST = V > 1;
     __shared__ double win[ST ? 2 : 1][ST ? kCgWin : 1];
     __shared__ double lds[kWaves * 2];
-    __shared__ double sum[kQuads * (MG ? 2 : 4)];
+    __shared__ double sum[kQuads * (MG ? 3 : 4)];
     __shared__ double cl[VG_NREG];
     __shared__ double mtab[8];
     if (threadIdx.x < VG_NREG) cl[threadIdx.x] = A.c[threadIdx.x];
     if (!MG && !REG && threadIdx.x < 7) mtab[threadIdx.x] = 1.0 / (1.0 + A.a * (double)threadIdx.x);
     __syncthreads();
-    double zbz, zq;   // (z, B z) and (z, q_old)
-    if constexpr (MG) {
-        const double *const p[2] = {part + P_ZBZ * A.ldp, part + P_ZQ * A.ldp};
-        const int G[2] = {Gp, Gp};
-        double v[2];
-        reduce_parts<2>(p, G, lds, v);
-        zbz = v[0];
-        zq = v[1];
-    } else {
-        zbz = reduce_parts(part + P_ZBZ * A.ldp, Gp, lds);
-        zq = scal[S_ZQ];
-    }
+    const double zbz = reduce_parts(part + P_ZBZ * A.ldp, Gp, lds);
     const double rz = scal[S_RZ + (k & 1)];
     const double aold = k > 0 ? scal[S_ALPHA + ((k & 1) ^ 1)] : 0.0;
     double beta = k > 0 ? rz / scal[S_RZ + ((k & 1) ^ 1)] : 0.0;
-    double pbp = k > 0 ? zbz + beta * (2.0 * zq + beta * scal[S_PQ]) : zbz;
+    double pbp = k > 0 ? zbz + beta * (2.0 * scal[S_ZQ] + beta * scal[S_PQ]) : zbz;
     if (pbp <= 0.0) {   // lost to rounding (B is positive definite): restart from p = z
         beta = 0.0;
         pbp = zbz;
@@ -504,7 +486,8 @@ __global__ __launch_bounds__(kBlock) void k_cg_step(CgArgs A, int k, int Gp, con
     if (blockIdx.x == 0 && threadIdx.x == 0) scal[S_ALPHA + (k & 1)] = alpha;
     const bool add = (k & 1) != 0, first = k == 0;   // p_old holds nothing before the first direction
     const int64_t nt = (A.n + kBlock * V - 1) / (kBlock * V);
-    double acc[MG ? 2 : 4] = {};   // (r.z, (z, q),) (p, q), r.r
+    constexpr int M = MG ? 3 : 4;
+    double acc[M] = {};   // (Jacobi: r.z,) (z, q) or (r, z_old), (p, q), r.r
     int64_t t = xcd_stride_tile(blockIdx.x, gridDim.x, 0, nt, A.run);
     CgIdx<NS> i[V];
     bool act[V];
@@ -591,20 +574,16 @@ __global__ __launch_bounds__(kBlock) void k_cg_step(CgArgs A, int k, int Gp, con
                 el(pnew, i[v]) = pi[v];
                 if (add) el(y, i[v]) = yi[v] + (aold * po[v] + alpha * pi[v]);
                 el(zr, i[v]) = MG ? rn : zn;
-                constexpr int Q = MG ? 0 : 2;
-                if constexpr (!MG) {
-                    acc[0] += rn * zn;
-                    acc[1] += zn * qi;
-                }
-                acc[Q] += pi[v] * qi;
-                acc[Q + 1] += rn * rn;
+                if constexpr (!MG) acc[0] += rn * zn;
+                acc[M - 3] += MG ? rn * zi[v] : zn * qi;
+                acc[M - 2] += pi[v] * qi;
+                acc[M - 1] += rn * rn;
             }
             i[v] = in[v];
             act[v] = an[v];
         }
     }
-    // (MG: the V-cycle writes r.z, k_cg_dot (z, q))
-    tile_sum_to<MG ? 2 : 4>(acc, sum, part + (MG ? P_PQ : P_RZ) * A.ldp + (int)blockIdx.x, A.ldp);
+    tile_sum_to<M>(acc, sum, part + (MG ? P_ZQ : P_RZ) * A.ldp + (int)blockIdx.x, A.ldp);   // (MG: the V-cycle writes r.z)
 }
 
 // The scalars of iterate k for the host (one block); k = 0: b.b too.
@@ -775,8 +754,8 @@ __global__ __launch_bounds__(kBlock) void k_mg_invd(const float *__restrict__ w,
 }
 
 // Fine-level residual of the pre-smoothed iterate x0 = w D^-1 r, which is
-// formed in registers for the voxel and its neighbours: t = r - B x0, one
-// thread per voxel.  With rr_part, first the convergence check of iterate k
+// formed in registers for the voxel and its neighbours: t = r - B x0, V voxels
+// per thread (staged form: kCgTileV).  With rr_part, first the convergence check of iterate k
 // from its Gp residual partials.
 template <bool REG, int NS, int V>
 __global__ __launch_bounds__(kBlock) void k_mg_res0(CgArgs A, int k, const double *__restrict__ r,
@@ -1264,7 +1243,7 @@ int cg_solve_t(vg_sim *h, int pool, double a, double rtol, int max_iter, int *it
             const int k = launched + it;
             hipLaunchKernelGGL((k_cg_dot<REG, NS, MG, V>), dim3(Gd), dim3(kBlock), 0, s, A, k,
                                MG ? mg_rz_blocks<REG, NS>(h) : (k > 0 ? Gs : Gi), Gs, (const double *)zb[k & 1],
-                               (const double *)h->cg_p[(k & 1) ^ 1], h->cg_scal, h->cg_part);
+                               h->cg_scal, h->cg_part);
             if ((rc = launch_status("k_cg_dot"))) return rc;
             hipLaunchKernelGGL((k_cg_step<REG, NS, MG, V>), dim3(Gs), dim3(kBlock), 0, s, A, k, Gd,
                                (const double *)zb[k & 1], (const double *)h->cg_p[(k & 1) ^ 1], h->cg_p[k & 1], h->cg_y,
